@@ -120,7 +120,9 @@ typedef struct {
     int32_t branching;       /* CUBICS_BRANCH_* */
     int32_t layout;          /* CUBICS_LAYOUT_*; AUTO uses the autotuned choice */
     int64_t split_target;    /* eager subtree splitting until this many subproblems were
-                                queued; 0 = no eager split (work is shared by donation) */
+                                queued; 0 = no eager split (with donation, count and all
+                                searches start with every worker on a share of the first
+                                branchings; then work is shared by donation) */
     int32_t *sol_buf;        /* device, caller-owned: sol_capacity x n int32 values, or NULL */
     uint64_t sol_capacity;   /* solutions that fit in sol_buf */
     int32_t workers;         /* persistent workers (wavefronts); 0 = fill the device */
@@ -248,9 +250,9 @@ int cubics_root(cubics_prob *prob, int32_t layout, uint32_t *out_bits, int32_t *
    Hitting max_nodes / max_solutions / time_ms is a verdict (LIMIT), not an
    error.  Workers check them periodically: max_nodes every 128 nodes of a
    worker, so a search may run up to 128 nodes per worker past it; a stop
-   (time_ms, cancel, another worker's find-first solution) is seen within
-   2048 nodes of a worker (the register layout without a node budget polls
-   that rarely: more frequent polls split its searches' tails too finely).
+   (time_ms, cancel, another worker's find-first solution) is seen about
+   every 20 us of a worker's own time, at its next node (the register layout:
+   within 16 nodes), the clock and the cancel flag about every millisecond.
    `limits` may be NULL (no limits, defaults). */
 int cubics_solve(cubics_prob *prob, int32_t mode, const cubics_limits *limits,
                  cubics_result *result);

@@ -163,6 +163,9 @@ struct SearchParams {
     uint32_t trail_words;  // per worker
     int32_t max_frames;    // frames per worker trail (a push beyond stops the launch)
     int32_t nworkers;
+    int32_t nblocks;       // workgroups of the search kernel
+    int32_t ring_workers;  // workers per ring (nworkers / nrings, rounded up)
+    int32_t team;          // 1 = the workers start their ring's first instances as teams
     int32_t donate;
     long long split_target;
     long long time_ticks;  // 0 = none (wall clock ticks)

@@ -1216,25 +1216,23 @@ DEV void stop_launch(const SearchParams &P, int reason) {
     signal_rings(P, SIG_STOP);
 }
 
+// Reserve the next position: one fetch-add on the tail.  (A compare-and-swap
+// made the donors of a search's tail race for the same word.)  Refused while
+// half of the cells are waiting to be claimed; the host sizes a ring for at
+// least twice its workers, so fewer than half a ring of producers can pass
+// that check at once, and the cell's previous position is always one whose
+// ticket was taken: its consumer copies the slot and hands the cell back
+// without waiting for anyone, so the wait below ends.
 DEV bool q_reserve(const SearchParams &P, uint32_t *cell, uint32_t *posout) {
-    uint32_t pos = ld_rlx(&P.q->tail);
-    for (;;) {
-        const uint32_t c = pos & P.qmask;
-        const uint32_t s = ld_rlx(&P.qseq[c]);
-        const int dif = (int)(s - pos);
-        if (dif == 0) {
-            if (cas_u32(&P.q->tail, &pos, pos + 1u)) {
-                slot_claimed();
-                *cell = c;
-                *posout = pos;
-                return true;
-            }
-        } else if (dif < 0) {
-            return false;
-        } else {
-            pos = ld_rlx(&P.q->tail);
-        }
-    }
+    const uint32_t tail = ld_rlx(&P.q->tail), head = ld_rlx(&P.q->head);
+    if ((int)(tail - head) >= (int)((P.qmask + 1u) >> 1)) return false;
+    const uint32_t pos = add_u(&P.q->tail, 1u);
+    const uint32_t c = pos & P.qmask;
+    while (ld_rlx(&P.qseq[c]) != pos) __builtin_amdgcn_s_sleep(1);
+    slot_claimed();
+    *cell = c;
+    *posout = pos;
+    return true;
 }
 
 // Push a FRAME task (branch variable x with the remaining values vals over the
@@ -1245,11 +1243,13 @@ DEV bool push_frame(const SearchParams &P, int inst, int x, int depth, const uin
     uint32_t cell = 0, pos = 0;
     int ok = 0;
     if (lane == 0) {
-        add_i(&P.g->pending, 1);
         ok = q_reserve(P, &cell, &pos) ? 1 : 0;
-        if (!ok) add_i(&P.g->pending, -1);
-        // the instance's live tasks count it before it is published
-        if (ok && P.nrings > 1) add_i(&P.ctl[inst].live, 1);
+        // counted as pending, and among its instance's live tasks, before it
+        // is published (this task is still pending itself)
+        if (ok) {
+            add_i(&P.g->pending, 1);
+            if (P.nrings > 1) add_i(&P.ctl[inst].live, 1);
+        }
     }
     ok = uni(ok);
     if (!ok) return false;
@@ -1392,31 +1392,158 @@ DEV void flush(InstCtl *ctl, Counters &C, int lane) {
     C.rev = C.bytes = C.ubytes = 0;
 }
 
-// Nodes between checks of stop flags and donation requests.  Each check may
-// donate a frame; in the register layout, where a node costs a fraction of a
-// microsecond, checking every 128 nodes split a search's tail into so many
-// small tasks that it ran for longer than the rest of the search (RB n=40
-// d=16 slice x0=1 with 6144 workers: 19 s at 128, 7.5 s at 512, 3.6 s at
-// 2048; checking after 128 nodes and then at doubling intervals brought the
-// small tasks back: 19 s).  The LDS layouts keep 128: their many-instance and
-// small searches need the faster spreading (13-queens: 20 ms at 128, 66 ms at
-// 512).
-constexpr int POLL = 128;
-constexpr int POLL_VAR = 2048;
-// The LDS layouts also poll once POLL_TICKS of wall clock (100 MHz ticks)
-// have passed since the last poll, after at least POLL_MIN nodes, and under
-// a node budget they count their nodes against it every ACCT_TICKS: when a
-// node takes a hundred microseconds (instances of a hundred variables and
-// thousands of table revisions per node), 128 nodes are tens of
-// milliseconds, during which idle workers wait for a donation, and an
-// instance shared by dozens of workers runs thousands of nodes past its
-// budget.  (A clock-based poll every 50 us made the fast nodes of small
-// count searches donate so often that their tails split into tiny tasks:
-// 200 instances of 12-18 variables took 4.7 s instead of 0.6 s.)
-constexpr int POLL_MIN = 8;
-constexpr long long POLL_TICKS = 100000;
-constexpr long long ACCT_TICKS = 5000;
+// Busy workers look at their ring every POLL_CLK core clocks (about 20 us):
+// the first wave of a workgroup to find the workgroup's view older than that
+// reads the ring's words, the others use its view in LDS, so that thousands
+// of waves do not load one word at a time.  The view holds the stop flags and
+// the odds (of 65536) with which a busy wave should donate: the tasks wanted
+// (idle waves beyond the queued tasks) over the busy waves, so that a few
+// idle waves do not make every busy one give work away.
+// The host's cancel flag (a read over PCIe) and the time limit are looked at
+// every SLOW_CLK (about 1 ms).
+constexpr uint32_t POLL_CLK = 48000;
+constexpr uint32_t SLOW_CLK = 2400000;
+// The register layout, where a node takes one or two microseconds, looks at
+// the clock every VAR_CHECK nodes; the LDS layouts at every node.
+constexpr int VAR_CHECK = 16;
+// Under a node budget, nodes are counted against it every ACCT_NODES nodes,
+// and in the LDS layouts also every ACCT_CLK (about 50 us) after at least
+// ACCT_MIN nodes: a node of an instance of a hundred variables takes up to a
+// hundred microseconds, and an instance shared by dozens of workers would run
+// thousands of nodes past its budget.
+constexpr int ACCT_NODES = 128;
+constexpr int ACCT_MIN = 8;
+constexpr uint32_t ACCT_CLK = 120000;
+// A frame is donated only if this many levels were seen below it in the
+// task: the frames of the last levels hold too few nodes to pay for a
+// hand-over (a few microseconds on either side).
+constexpr int DONATE_LEVELS = 2;
+// Longest back-off of an idle wave between two polls of its queue cell.
+constexpr int BACKOFF_MAX = 8;
 
+DEV uint32_t clk() { return (uint32_t)clock64(); }
+
+struct WgPoll {  // in LDS, one per workgroup
+    uint32_t time, slow;  // clock of the last refresh, of the last slow check
+    uint32_t sig, odds;   // the ring's signal word, the donation odds
+};
+
+// The workgroup's view of its ring, refreshed when older than POLL_CLK.
+// Returns the signal word (SIG_STOP also when this call stopped the launch).
+DEV uint32_t wg_poll(const SearchParams &P, WgPoll *w, uint32_t now, long long t_start, int lane, uint32_t *odds) {
+    uint32_t sig = 0u, od = 0u;
+    if (lane == 0) {
+        if ((int)(now - lds_ld(&w->time)) >= (int)POLL_CLK) {
+            lds_st(&w->time, now);
+            sig = ld_rlx(&P.q->signal);
+            const int idle = (int)(sig & SIG_IDLE_MASK);
+            if (P.donate && idle > 0) {
+                const int queued = (int)(ld_rlx(&P.q->tail) - ld_rlx(&P.q->head));
+                const int want = idle - (queued > 0 ? queued : 0);
+                const int busy = P.ring_workers - idle;
+                if (want > 0) od = want >= busy ? 65536u : (uint32_t)(((long long)want << 16) / busy);
+            }
+            if ((P.time_ticks || P.cancel) && (int)(now - lds_ld(&w->slow)) >= (int)SLOW_CLK) {
+                lds_st(&w->slow, now);
+                int st = 0;
+                if (P.time_ticks && (long long)wall_clock64() - t_start > P.time_ticks) st = 2;
+                if (P.cancel && *P.cancel) st = 3;
+                if (st) {
+                    stop_launch(P, st);
+                    sig |= SIG_STOP;
+                }
+            }
+            lds_st(&w->sig, sig);
+            lds_st(&w->odds, od);
+        } else {
+            sig = lds_ld(&w->sig);
+            od = lds_ld(&w->odds);
+        }
+    }
+    *odds = uniu(od);
+    return uniu(sig);
+}
+
+// The values of v that a donor gives away: the upper half of them (all of
+// them when there is one).
+template <int WM>
+DEV void upper_half(const uint32_t (&v)[WM], uint32_t (&give)[WM]) {
+    int k = 0;
+#pragma unroll
+    for (int q = 0; q < WM; ++q) {
+        give[q] = v[q];
+        k += __popc(v[q]);
+    }
+    for (int drop = k / 2; drop > 0; --drop) {
+        bool done = false;
+#pragma unroll
+        for (int q = 0; q < WM; ++q)
+            if (!done && give[q]) {
+                give[q] &= give[q] - 1u;
+                done = true;
+            }
+    }
+}
+
+// The part of a branching's values v (m of them) that member `rank` of a team
+// of `size` <= m takes: values number rank, rank + size, ...
+template <int WM>
+DEV void dealt_values(const uint32_t (&v)[WM], int rank, int size, uint32_t (&own)[WM]) {
+    int turn = 0;
+#pragma unroll
+    for (int q = 0; q < WM; ++q) {
+        own[q] = 0u;
+        uint32_t bits = v[q];
+        while (bits) {
+            if (turn == rank) own[q] |= bits & (0u - bits);
+            turn = turn + 1 == size ? 0 : turn + 1;
+            bits &= bits - 1u;
+        }
+    }
+}
+// Value number k (from 0) of v, as a one-value domain.
+template <int WM>
+DEV void nth_value(const uint32_t (&v)[WM], int k, uint32_t (&one)[WM]) {
+    int left = k;
+#pragma unroll
+    for (int q = 0; q < WM; ++q) {
+        const int pc = __popc(v[q]);
+        one[q] = 0u;
+        if (left >= 0 && left < pc) {
+            uint32_t bits = v[q];
+            for (int z = 0; z < left; ++z) bits &= bits - 1u;
+            one[q] = bits & (0u - bits);
+        }
+        left -= pc;
+    }
+}
+
+// A team: the workers that start one instance together (count and all modes).
+// Every member propagates the root; then the team divides itself over the
+// children of each branching, child k taking members [ceil(k g / m),
+// ceil((k + 1) g / m)) of g over m children, until a member is alone or its
+// team is no larger than the branching, whose values are then dealt out.  So
+// thousands of workers hold subtrees of their own after a few node times,
+// without touching the queue; only a team's first member counts its nodes.
+// Before, one worker opened the tree and gave a frame away every 128 nodes
+// (2048 in the register layout), and a frame went as a whole: with the polls
+// below and half-frame donations, 13-queens with 8 blocked squares (3.4e5
+// nodes) went from 89 to 1.4 ms, RB n=40 d=16 tightness 0.40 (1e5..1e6 nodes)
+// from 379 to 9 ms, a batch of 768 labels from 78 to 16 ms, 48 global twins
+// from 177 to 22 ms; the RB slice of 1.34e10 nodes from 3.5 to 3.2 s.
+struct Team {
+    int rank, size;
+};
+// This member's child of a branching with m < size children; narrows T.
+// (Integer division runs on the vector unit: uni() keeps its results, and
+// all that is derived from them, in scalar registers.)
+DEV int team_child(Team &T, int m) {
+    const int k = uni(T.rank * m / T.size);
+    const int lo = uni((k * T.size + m - 1) / m), hi = uni(((k + 1) * T.size + m - 1) / m);
+    T.rank -= lo;
+    T.size = hi - lo;
+    return k;
+}
 
 // ------------------------------------------------------ branching policy
 
@@ -1634,14 +1761,15 @@ DEV int choose_explore(const InstDev &I, const Lds &L, int lane, u64 rnd) {
 // register budget).
 template <int WM, int FEAT, bool GLOB, bool SEGC, bool GM>
 DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, int kind,
-                  Frame<WM> F0, const Lds &L, uint32_t *trail, Counters &C, int lane,
-                  long long t_start, const PolicyDev &LP, const PolicyDev &VP) {
+                  Frame<WM> F0, Team T, const Lds &L, uint32_t *trail, Counters &C, int lane,
+                  long long t_start, WgPoll *wgp, const PolicyDev &LP, const PolicyDev &VP) {
     const int n = I.n, W = I.W, nw = n * W;
     const int layout = P.layout;
     const uint32_t FW = P.frame_words;
     int sp = 0;
     Frame<WM> F;
     bool have_open = false, need_restore = false;
+    bool at_node = false;  // the node to propagate next is in L.dom (a root or a team's node)
     // register copy of the top frame's snapshot (lane-per-word), so that the
     // siblings under one frame are restored without an HBM round trip
     constexpr int NC = WM <= 2 ? 4 : 1;
@@ -1649,10 +1777,13 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
     uint32_t snapc[NC];
     bool snap_valid = false;
     int depth = F0.depth;
-    int since_poll = 0, polls = 0;
+    int since_poll = 0, since_acct = 0, deepest = 0;
     // clock of the task's last poll (a task starts as if it had just polled)
-    long long last_poll = (long long)wall_clock64(), last_acct = last_poll;
+    uint32_t last_poll = clk(), last_acct = last_poll;
     int open_x = 0;
+    uint32_t own[WM];  // the values of the next branching that are this worker's
+#pragma unroll
+    for (int k = 0; k < WM; ++k) own[k] = 0xFFFFFFFFu;
     const bool tracing = FEAT == 2 && P.trace_out != nullptr;
     const bool learned = FEAT == 1 && P.branching == 1;
     // learned value order (d-way): the value network's score keys of the top
@@ -1675,18 +1806,16 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
             for (int k = 0; k < W; ++k) atomicAnd(&L.dom[v * W + k], I.rows[off + k]);
         }
         wsync();
-        C.nodes += 1;
-        C.stamp += 1;
         int bx = 0;
-        int st = node_test<WM>(I, L, lane, &bx);
-        if (st == 2) { C.fails += 1; return; }
+        if (node_test<WM>(I, L, lane, &bx) == 2) {
+            C.nodes += T.rank == 0 ? 1 : 0;
+            C.stamp += 1;
+            C.fails += T.rank == 0 ? 1 : 0;
+            return;
+        }
         dirty_all(L, n, lane);
-        if (propagate<WM, GLOB, SEGC, GM>(I, L, layout, C, lane)) { C.fails += 1; return; }
-        st = node_test<WM>(I, L, lane, &bx);
-        if (st == 1) { record_solution<WM>(P, I, ctl, L, C, lane); return; }
-        have_open = true;
-        open_x = bx;
         depth = 0;
+        at_node = true;
     } else {
         // FRAME task: the snapshot is in L.dom; it becomes trail frame 0
         F = F0;
@@ -1727,7 +1856,11 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
             }
             uint32_t dx[WM];
 #pragma unroll
-            for (int k = 0; k < WM; ++k) dx[k] = k < W ? uniu(L.dom[x * W + k]) : 0u;
+            for (int k = 0; k < WM; ++k) {
+                dx[k] = k < W ? uniu(L.dom[x * W + k]) & own[k] : 0u;
+                own[k] = 0xFFFFFFFFu;
+            }
+            deepest = depth > deepest ? depth : deepest;
             int side0 = 0;
             if (split) {
                 // one FRAME task per child of x, each over this node's domains
@@ -1824,7 +1957,7 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
         }
     next_child:
         // take the next value of the top frame, popping exhausted frames
-        for (;;) {
+        while (!at_node) {
             if (sp == 0) return;
             bool emptyv = true;
 #pragma unroll
@@ -1861,7 +1994,7 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
             }
             break;
         }
-        {
+        if (!at_node) {
             // the child's domain of x: the smallest remaining value, or (2-way,
             // second child) all the remaining values
             uint32_t cv[WM];
@@ -1918,81 +2051,99 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
             depth = F.depth + 1;
             dirty_one(L, n, F.x, lane);
         }
-        C.nodes += 1;
+        C.nodes += T.rank == 0 ? 1 : 0;
         C.stamp += 1;
         {
             const bool failed = propagate<WM, GLOB, SEGC, GM>(I, L, layout, C, lane);
             if (failed) {
-                C.fails += 1;
-                if ((tracing || learned) && lane == 0) L.fails[F.x] += 1u;
+                C.fails += T.rank == 0 ? 1 : 0;
+                if ((tracing || learned) && lane == 0 && sp > 0) L.fails[F.x] += 1u;
+                if (at_node) return;
             } else {
                 int bx = 0;
                 const int st = node_test<WM>(I, L, lane, &bx);
                 if (st == 1) {
-                    record_solution<WM>(P, I, ctl, L, C, lane);
-                    if (P.mode == 0) return;  // first mode: one solution ends the instance
+                    if (T.rank == 0) record_solution<WM>(P, I, ctl, L, C, lane);
+                    if (at_node || P.mode == 0) return;  // first mode: one solution ends the instance
                 } else {
                     have_open = true;
                     open_x = bx;
                 }
             }
         }
-        // periodic checks: stop flags and the node budget (every POLL nodes,
-        // and under a budget also every POLL_TICKS), then the clock, the
-        // cancel flag and donation (every POLL nodes only: donating more
-        // often splits a search's tail into too many small tasks)
-        ++since_poll;
-        bool due = since_poll >= POLL, acct = due;
-        if (!due && since_poll >= POLL_MIN) {
-            const long long now = (long long)wall_clock64();
-            due = now - last_poll >= POLL_TICKS;
-            acct = due || (I.max_nodes && now - last_acct >= ACCT_TICKS);
+        if (at_node) {
+            if (T.size <= 1) {
+                at_node = false;
+                continue;
+            }
+            // the team's share of this branching (see Team)
+            const int x = learned ? choose_learned<WM>(LP, I, L, depth, lane, open_x) : open_x;
+            uint32_t dx[WM], cv[WM];
+            int m = 0;
+#pragma unroll
+            for (int k = 0; k < WM; ++k) {
+                dx[k] = k < W ? uniu(L.dom[x * W + k]) : 0u;
+                m += __popc(dx[k]);
+            }
+            if (!P.two_way && T.size <= m) {
+                dealt_values<WM>(dx, T.rank, T.size, own);
+                T = {0, 1};
+                at_node = false;
+                continue;
+            }
+            // child k: value number k; 2-way: x = min, then x in the rest
+            const int k = team_child(T, P.two_way ? 2 : m);
+            nth_value<WM>(dx, P.two_way ? 0 : k, cv);
+            if (P.two_way && k)
+#pragma unroll
+                for (int q = 0; q < WM; ++q) cv[q] = dx[q] & ~cv[q];
+            if (lane < W) {
+                uint32_t w = 0u;
+#pragma unroll
+                for (int q = 0; q < WM; ++q)
+                    if (q == lane) w = cv[q];
+                L.dom[x * W + lane] = w;
+            }
+            have_open = false;
+            ++depth;
+            dirty_one(L, n, x, lane);
+            continue;
         }
-        if (acct) {
-            const long long now = (long long)wall_clock64();
+        // periodic checks (by the core clock, see POLL_CLK): the node budget,
+        // the stop flags, and whether to donate
+        ++since_poll;
+        ++since_acct;
+        const uint32_t now = clk();
+        if (I.max_nodes && (since_acct >= ACCT_NODES || (since_acct >= ACCT_MIN && now - last_acct >= ACCT_CLK))) {
+            since_acct = 0;
             last_acct = now;
-            if (due) last_poll = now;
-            // one shared word per poll; stop, done and queue words only when
-            // it says so
-            int stop = 0, want = 0;
-            if (lane == 0) {
-                const uint32_t sig = ld_rlx(&P.q->signal);
-                stop = (sig & SIG_STOP) ? 1 : ((sig & SIG_DONE) ? ld_rlx_i(&ctl->done) : 0);
-                // donate while fewer tasks wait unclaimed than waves are idle
-                // (a negative difference: tickets waiting for a task)
-                const int idle = (int)(sig & SIG_IDLE_MASK);
-                if (due && P.donate && idle > 0)
-                    want = (int)(ld_rlx(&P.q->tail) - ld_rlx(&P.q->head)) < idle;
+            u64 tot = 0;
+            if (lane == 0) tot = add_u64(&ctl->nodes, C.nodes) + C.nodes;
+            tot = uni64(tot);
+            C.nodes = 0;
+            if (tot >= I.max_nodes) {
+                if (lane == 0) { ctl->reason = 2; st_rel_i(&ctl->done, 1); signal_rings(P, SIG_DONE); }
+                return;
             }
-            stop = uni(stop);
-            if (stop) return;
-            if (I.max_nodes) {
-                u64 tot = 0;
-                if (lane == 0) tot = add_u64(&ctl->nodes, C.nodes) + C.nodes;
-                tot = uni64(tot);
-                C.nodes = 0;
-                if (tot >= I.max_nodes) {
-                    if (lane == 0) { ctl->reason = 2; st_rel_i(&ctl->done, 1); signal_rings(P, SIG_DONE); }
-                    return;
-                }
-            }
-            if (due) {
+        }
+        if (now - last_poll >= POLL_CLK) {
+            // nodes so long that hardly one fits between two polls are worth
+            // a hand-over each
+            const int levels = since_poll <= 2 ? 0 : DONATE_LEVELS;
+            last_poll = now;
             since_poll = 0;
-            // the clock and the host's cancel flag (a read over PCIe) every
-            // 16th poll
-            if ((P.time_ticks || P.cancel) && (++polls & 15) == 0) {
-                int st2 = 0;
-                if (lane == 0) {
-                    if (P.time_ticks && (long long)wall_clock64() - t_start > P.time_ticks) st2 = 2;
-                    if (P.cancel && *P.cancel) st2 = 3;
-                    if (st2) stop_launch(P, st2);
-                }
-                if (uni(st2)) return;
+            uint32_t odds = 0u;
+            const uint32_t sig = wg_poll(P, wgp, now, t_start, lane, &odds);
+            if (sig & SIG_STOP) return;
+            if (sig & SIG_DONE) {
+                int done = 0;
+                if (lane == 0) done = ld_rlx_i(&ctl->done);
+                if (uni(done)) return;
             }
-            if (uni(want) && sp > 0) {
-                // donate the shallowest frame that still has untried values
-                int tsel = -1;
+            if (odds && sp > 0 && (uint32_t)(mix64(C.stamp ^ ((u64)now << 32) ^ (u64)(size_t)trail) & 0xFFFFu) < odds) {
+                // the shallowest frame that still has untried values
                 // (frames below the top keep their values in HBM; the top's are in F)
+                int tsel = -1;
                 bool topnz = false;
 #pragma unroll
                 for (int k = 0; k < WM; ++k) topnz |= F.v[k] != 0u;
@@ -2012,19 +2163,39 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
                     Frame<WM> D;
                     frame_load_meta<WM>(f, D);
                     if (tsel == sp - 1) D = F;
-                    if (push_frame<WM>(P, b, D.x, D.depth, D.v, f + FRAME_HDR, nw, lane, D.side)) {
-                        if (lane < WM) f[4 + lane] = 0u;
+                    // d-way: half of the frame's values, so that both sides
+                    // can share again; 2-way: all that is left of the frame.
+                    // A worker keeps something for itself.
+                    const bool more = tsel < sp - 1 || have_open;
+                    uint32_t give[WM];
+                    bool keeps = false;
+                    if (P.two_way) {
+#pragma unroll
+                        for (int k = 0; k < WM; ++k) give[k] = D.v[k];
+                    } else {
+                        upper_half<WM>(D.v, give);
+                    }
+#pragma unroll
+                    for (int k = 0; k < WM; ++k) keeps |= (D.v[k] & ~give[k]) != 0u;
+                    if ((more || keeps) && deepest - D.depth >= levels &&
+                        push_frame<WM>(P, b, D.x, D.depth, give, f + FRAME_HDR, nw, lane, D.side)) {
+                        if (lane < WM) {
+                            uint32_t v = 0u;
+#pragma unroll
+                            for (int k = 0; k < WM; ++k)
+                                if (k == lane) v = D.v[k] & ~give[k];
+                            f[4 + lane] = v;
+                        }
                         if (tracing)
                             for (int t = lane; t <= tsel; t += 64) trail[(size_t)t * FW + 2] = 1u;
                         if (tsel == sp - 1) {
 #pragma unroll
-                            for (int k = 0; k < WM; ++k) F.v[k] = 0u;
+                            for (int k = 0; k < WM; ++k) F.v[k] &= ~give[k];
                         }
                         C.steals += 1;
                     }
                 }
             }
-            }  // due
         }
     }
 }
@@ -2186,19 +2357,18 @@ DEV int node_test_var(int n, uint32_t d, int lane, int *bx) {
 // is prefetched into a register, so that returning one level needs no wait.
 template <int WM>
 DEV void run_task_var(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, int kind,
-                      Frame<WM> F0, const Lds &L, uint32_t *trail, Counters &C, int lane,
-                      long long t_start) {
+                      Frame<WM> F0, Team T, const Lds &L, uint32_t *trail, Counters &C, int lane,
+                      long long t_start, WgPoll *wgp) {
     const int n = I.n;
     const uint32_t FW = P.frame_words;
     int sp = 0;
     Frame<WM> F;  // the top frame (sp - 1)
     bool have_open = false, need_restore = false;
     int depth = F0.depth;
-    int since_poll = 0, polls = 0;
-    // a node budget is checked at every poll: keep it as fine as in the LDS
-    // layouts when there is one
-    const int poll_iv = I.max_nodes ? POLL : POLL_VAR;
+    int until_check = VAR_CHECK, since_acct = 0, deepest = 0;
+    uint32_t last_poll = clk();
     int open_x = 0;
+    uint32_t own = 0xFFFFFFFFu;  // the values of the next branching that are this worker's
     uint32_t d = lane < n ? L.dom[lane] : 0u;
     uint32_t snapc = 0u, snapp = 0u;  // snapshots of frames sp - 1 and sp - 2
     bool snap_valid = false, snapp_valid = false;
@@ -2210,22 +2380,50 @@ DEV void run_task_var(const SearchParams &P, const InstDev &I, InstCtl *ctl, int
             const int v = I.unary[2 * t], off = I.unary[2 * t + 1];
             if (lane == v) d &= I.rows[off];
         }
-        C.nodes += 1;
-        C.stamp += 1;
         int bx = 0;
-        if (node_test_var(n, d, lane, &bx) == 2) { C.fails += 1; return; }
-        const u64 all = n >= 64 ? ~0ull : ((1ull << n) - 1ull);
-        if (propagate_var(I, d, all, C, lane)) { C.fails += 1; return; }
-        const int st = node_test_var(n, d, lane, &bx);
-        if (st == 1) {
-            if (lane < n) L.dom[lane] = d;
-            wsync();
-            record_solution<WM>(P, I, ctl, L, C, lane);
+        if (node_test_var(n, d, lane, &bx) == 2) {
+            C.nodes += T.rank == 0 ? 1 : 0;
+            C.fails += T.rank == 0 ? 1 : 0;
             return;
+        }
+        // the root and, in a team, the nodes down to this worker's own part
+        // (a loop of its own: the search loop below is bound by scalar issue)
+        u64 dirty = n >= 64 ? ~0ull : ((1ull << n) - 1ull);
+        depth = 0;
+        for (;;) {
+            C.nodes += T.rank == 0 ? 1 : 0;
+            if (propagate_var(I, d, dirty, C, lane)) {
+                C.fails += T.rank == 0 ? 1 : 0;
+                return;
+            }
+            if (node_test_var(n, d, lane, &bx) == 1) {
+                if (T.rank == 0) {
+                    if (lane < n) L.dom[lane] = d;
+                    wsync();
+                    record_solution<WM>(P, I, ctl, L, C, lane);
+                }
+                return;
+            }
+            if (T.size <= 1) break;
+            const uint32_t dx1[1] = {(uint32_t)__builtin_amdgcn_readlane((int)d, bx)};
+            const int m = __popc(dx1[0]);
+            uint32_t cv[1];
+            if (!P.two_way && T.size <= m) {
+                uint32_t o[1];
+                dealt_values<1>(dx1, T.rank, T.size, o);
+                own = o[0];
+                break;
+            }
+            // child k: value number k; 2-way: x = min, then x in the rest
+            const int k = team_child(T, P.two_way ? 2 : m);
+            nth_value<1>(dx1, P.two_way ? 0 : k, cv);
+            if (P.two_way && k) cv[0] = dx1[0] & ~cv[0];
+            if (lane == bx) d = cv[0];
+            ++depth;
+            dirty = 1ull << bx;
         }
         have_open = true;
         open_x = bx;
-        depth = 0;
     } else {
         F = F0;
         if (lane < n) trail[FRAME_HDR + lane] = d;
@@ -2245,7 +2443,9 @@ DEV void run_task_var(const SearchParams &P, const InstDev &I, InstCtl *ctl, int
                 prod = unill(prod);
                 if (prod < P.split_target) split = true;
             }
-            uint32_t dx = (uint32_t)__builtin_amdgcn_readlane((int)d, x);
+            uint32_t dx = (uint32_t)__builtin_amdgcn_readlane((int)d, x) & own;
+            own = 0xFFFFFFFFu;
+            deepest = depth > deepest ? depth : deepest;
             int side0 = 0;
             if (split) {
                 if (lane < n) L.dom[lane] = d;
@@ -2366,7 +2566,6 @@ DEV void run_task_var(const SearchParams &P, const InstDev &I, InstCtl *ctl, int
             depth = F.depth + 1;
         }
         C.nodes += 1;
-        C.stamp += 1;
         if (propagate_var(I, d, 1ull << F.x, C, lane)) {
             C.fails += 1;
         } else {
@@ -2385,23 +2584,11 @@ DEV void run_task_var(const SearchParams &P, const InstDev &I, InstCtl *ctl, int
                 open_x = bx;
             }
         }
-        if (++since_poll >= poll_iv) {
-            fold_var(C);
-            since_poll = 0;
-            // one shared word per poll; stop, done and queue words only when
-            // it says so
-            int stop = 0, want = 0;
-            if (lane == 0) {
-                const uint32_t sig = ld_rlx(&P.q->signal);
-                stop = (sig & SIG_STOP) ? 1 : ((sig & SIG_DONE) ? ld_rlx_i(&ctl->done) : 0);
-                // donate while fewer tasks wait unclaimed than waves are idle
-                // (a negative difference: tickets waiting for a task)
-                const int idle = (int)(sig & SIG_IDLE_MASK);
-                if (P.donate && idle > 0)
-                    want = (int)(ld_rlx(&P.q->tail) - ld_rlx(&P.q->head)) < idle;
-            }
-            if (uni(stop)) return;
-            if (I.max_nodes) {
+        if (--until_check == 0) {
+            until_check = VAR_CHECK;
+            since_acct += VAR_CHECK;
+            if (since_acct >= ACCT_NODES) fold_var(C);
+            if (I.max_nodes && since_acct >= ACCT_NODES) {
                 u64 tot = 0;
                 if (lane == 0) tot = add_u64(&ctl->nodes, C.nodes) + C.nodes;
                 tot = uni64(tot);
@@ -2411,39 +2598,50 @@ DEV void run_task_var(const SearchParams &P, const InstDev &I, InstCtl *ctl, int
                     return;
                 }
             }
-            // the clock and the host's cancel flag (a read over PCIe) every
-            // 2048 nodes
-            if ((P.time_ticks || P.cancel) && (++polls & (poll_iv == POLL ? 15 : 0)) == 0) {
-                int st2 = 0;
-                if (lane == 0) {
-                    if (P.time_ticks && (long long)wall_clock64() - t_start > P.time_ticks) st2 = 2;
-                    if (P.cancel && *P.cancel) st2 = 3;
-                    if (st2) stop_launch(P, st2);
+            if (since_acct >= ACCT_NODES) since_acct = 0;
+            const uint32_t now = clk();
+            if (now - last_poll >= POLL_CLK) {
+                last_poll = now;
+                uint32_t odds = 0u;
+                const uint32_t sig = wg_poll(P, wgp, now, t_start, lane, &odds);
+                if (sig & SIG_STOP) return;
+                if (sig & SIG_DONE) {
+                    int done = 0;
+                    if (lane == 0) done = ld_rlx_i(&ctl->done);
+                    if (uni(done)) return;
                 }
-                if (uni(st2)) return;
-            }
-            if (uni(want) && sp > 0) {
-                // donate the shallowest frame that still has untried values
-                const u64 m = __ballot(lane < sp - 1 && mval != 0u);
-                int tsel = m ? __ffsll((long long)m) - 1 : -1;
-                if (tsel < 0 && F.v[0] != 0u) tsel = sp - 1;
-                if (tsel >= 0) {
-                    uint32_t *f = trail + (size_t)tsel * FW;
-                    Frame<WM> D;
-                    if (tsel == sp - 1) {
-                        D = F;
-                    } else {
-                        D.x = __builtin_amdgcn_readlane(mx, tsel);
-                        D.depth = __builtin_amdgcn_readlane(mdep, tsel);
-                        D.side = __builtin_amdgcn_readlane(mside, tsel);
-                        D.v[0] = (uint32_t)__builtin_amdgcn_readlane((int)mval, tsel);
+                if (odds && sp > 0 &&
+                    (uint32_t)(mix64(((u64)now << 32) ^ (u64)(size_t)trail) & 0xFFFFu) < odds) {
+                    // the shallowest frame that still has untried values
+                    const u64 m = __ballot(lane < sp - 1 && mval != 0u);
+                    int tsel = m ? __ffsll((long long)m) - 1 : -1;
+                    if (tsel < 0 && F.v[0] != 0u) tsel = sp - 1;
+                    if (tsel >= 0) {
+                        uint32_t *f = trail + (size_t)tsel * FW;
+                        Frame<WM> D;
+                        if (tsel == sp - 1) {
+                            D = F;
+                        } else {
+                            D.x = __builtin_amdgcn_readlane(mx, tsel);
+                            D.depth = __builtin_amdgcn_readlane(mdep, tsel);
+                            D.side = __builtin_amdgcn_readlane(mside, tsel);
+                            D.v[0] = (uint32_t)__builtin_amdgcn_readlane((int)mval, tsel);
 #pragma unroll
-                        for (int k = 1; k < WM; ++k) D.v[k] = 0u;
-                    }
-                    if (push_frame<WM>(P, b, D.x, D.depth, D.v, f + FRAME_HDR, n, lane, D.side)) {
-                        if (tsel == sp - 1) F.v[0] = 0u;
-                        else if (lane == tsel) mval = 0u;
-                        C.steals += 1;
+                            for (int k = 1; k < WM; ++k) D.v[k] = 0u;
+                        }
+                        // what to give: as in run_task
+                        const bool more = tsel < sp - 1 || have_open;
+                        const uint32_t v1[1] = {D.v[0]};
+                        uint32_t g1[1] = {D.v[0]};
+                        if (!P.two_way) upper_half<1>(v1, g1);
+                        const uint32_t left = D.v[0] & ~g1[0];
+                        D.v[0] = g1[0];
+                        if ((more || left) && deepest - D.depth >= DONATE_LEVELS &&
+                            push_frame<WM>(P, b, D.x, D.depth, D.v, f + FRAME_HDR, n, lane, D.side)) {
+                            if (tsel == sp - 1) F.v[0] = left;
+                            else if (lane == tsel) mval = left;
+                            C.steals += 1;
+                        }
                     }
                 }
             }
@@ -2482,24 +2680,41 @@ DEV InstDev rebase(const InstDev &g, const uint32_t *tab) {
 #ifndef CUBICS_LB_WAVES
 #define CUBICS_LB_WAVES 4
 #endif
+// ... and of the register layout, whose nodes wait on each other alone: six
+// waves per SIMD hide more of it.
+#ifndef CUBICS_LB_WAVES_VAR
+#define CUBICS_LB_WAVES_VAR 6
+#endif
 
 // Persistent search kernel: every wavefront is a worker that pops tasks from
 // the global queue until no task is pending anywhere.  TL: a single-instance
 // solve whose packed tables are staged once per workgroup in LDS.
 template <int WM, bool TL, int FEAT, bool GLOB, bool SEGC, bool VAR = false>
-__global__ __launch_bounds__(512, WM <= 2 ? CUBICS_LB_WAVES : 1) void search_kernel(SearchParams P) {
-    extern __shared__ uint32_t lds_raw[];
+__global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_LB_WAVES : 1)) void search_kernel(SearchParams P) {
+    // 16-byte alignment: the words behind hold 64-bit sets that lanes update
+    // with 64-bit atomics, and the tables are staged by 16-byte stores
+    extern __shared__ __align__(16) uint32_t lds_raw[];
     // idle_token: 1 while one idle wave of this workgroup polls the global
     // queue; drained: set once that wave saw no task pending anywhere
     __shared__ uint32_t idle_token, drained;
+    // team_left: this workgroup's waves that still work on their share of a
+    // team's start (the workgroup's share counts as one pending task)
+    __shared__ uint32_t team_left;
+    __shared__ WgPoll wgp;
+    // (uni(): keeps what is derived from the launch shape in scalar registers)
+    const int bid = uni((int)blockIdx.x), wpb = uni((int)(blockDim.x >> 6));
+    const int wg_waves = min(P.nworkers - bid * wpb, wpb);
     if (threadIdx.x == 0) {
         idle_token = 0u;
         drained = 0u;
+        team_left = (uint32_t)wg_waves;
+        wgp.time = wgp.slow = clk();
+        wgp.sig = wgp.odds = 0u;
     }
     __syncthreads();
     const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int wid = blockIdx.x * (blockDim.x >> 6) + wave;
+    const int wave = uni((int)(threadIdx.x >> 6));
+    const int wid = bid * wpb + wave;
     uint32_t tab_words = 0;
     InstDev IL;
     if (TL) {
@@ -2570,7 +2785,7 @@ __global__ __launch_bounds__(512, WM <= 2 ? CUBICS_LB_WAVES : 1) void search_ker
     uint32_t *trail = P.trail + (size_t)wid * P.trail_words;
     // the workgroup's ring (with one ring per XCD, workgroup b runs on XCD
     // b % 8, as the hardware deals workgroups out in turn)
-    const int ring = P.nrings > 1 ? (int)(blockIdx.x % (unsigned)P.nrings) : 0;
+    const int ring = P.nrings > 1 ? uni(bid % P.nrings) : 0;
     P.q = &P.qb->ring[ring];
     P.qseq += (size_t)ring * (P.qmask + 1u);
     P.qdata += (size_t)ring * (P.qmask + 1u) * P.slot_words;
@@ -2580,9 +2795,37 @@ __global__ __launch_bounds__(512, WM <= 2 ? CUBICS_LB_WAVES : 1) void search_ker
     // an instance this worker admitted (rings > 1): its ROOT task runs next,
     // on this worker, without passing through the queue
     int direct = -1;
+    // Instance whose counters C holds, not yet added to its control block:
+    // without a node budget they are added when the worker turns to another
+    // instance and at its end (eight atomics on one line per task, from
+    // thousands of workers, held up a search's tail).
+    int held = -1;
+    // Without donation, eager split and admission no task is ever queued after
+    // the launch: an idle wave whose ticket lies past the last one can leave.
+    const bool fixed_tasks = !P.donate && P.split_target == 0 && P.nrings == 1;
+    // A team's start (P.team): the workgroups of a ring are dealt to its
+    // first instances, and every wave of them takes its share.
+    Team T = {0, 1};
+    bool team = false;
+    if (P.team) {
+        const int R = P.nrings;
+        const int slots = uni(P.B > ring ? min(P.seeded, (P.B - ring + R - 1) / R) : 0);
+        const int nb = uni((P.nblocks - ring + R - 1) / R), jb = uni(bid / R);
+        if (slots > 0) {
+            const int slot = uni(jb % slots);
+            const int blocks = uni((nb - slot + slots - 1) / slots);
+            // the grid's last workgroup may hold fewer workers
+            const int last = P.nblocks - 1;
+            const int miss = uni(last % R == ring && (last / R) % slots == slot ? P.nblocks * wpb - P.nworkers : 0);
+            T.rank = uni(jb / slots) * wpb + wave;
+            T.size = blocks * wpb - miss;
+            direct = slot * R + ring;
+            team = true;
+        }
+    }
     // Idle waves: only the one holding its workgroup's token takes a ticket
-    // and waits on its cell (backing off exponentially, up to ~27 us between
-    // polls); the others wait on the token in LDS.  A wave holding a ticket
+    // and waits on its cell (backing off exponentially, up to BACKOFF_MAX
+    // sleeps of 2048 clocks between polls); the others wait on the token in LDS.  A wave holding a ticket
     // leaves when no task is pending anywhere (no task can appear again), and
     // tells its workgroup through LDS.
     int backoff = 1;
@@ -2617,7 +2860,8 @@ __global__ __launch_bounds__(512, WM <= 2 ? CUBICS_LB_WAVES : 1) void search_ker
                 }
                 if (lane == 0) {
                     got = ld_rlx(&P.qseq[ticket & P.qmask]) == ticket + 1u;
-                    if (!got && (++polls & 1) == 0 && ld_rlx_i(&P.g->pending) == 0) {
+                    if (!got && (++polls & 1) == 0 &&
+                        (ld_rlx_i(&P.g->pending) == 0 || (fixed_tasks && (int)(ticket - ld_rlx(&P.q->tail)) >= 0))) {
                         fin = 1;
                         lds_st(&drained, 1u);
                     }
@@ -2632,7 +2876,7 @@ __global__ __launch_bounds__(512, WM <= 2 ? CUBICS_LB_WAVES : 1) void search_ker
                 if (uni(fin)) break;
                 if (poller) {
                     for (int z = 0; z < backoff; ++z) __builtin_amdgcn_s_sleep(32);
-                    backoff = backoff < 32 ? backoff * 2 : 32;
+                    backoff = backoff < BACKOFF_MAX ? backoff * 2 : BACKOFF_MAX;
                 } else {
                     __builtin_amdgcn_s_sleep(16);
                 }
@@ -2661,6 +2905,8 @@ __global__ __launch_bounds__(512, WM <= 2 ? CUBICS_LB_WAVES : 1) void search_ker
         }
         const InstDev I = TL ? IL : P.inst[b];
         const int nw = I.n * I.W;
+        if (held >= 0 && held != b) flush<WM>(P.ctl + held, C, lane);
+        held = b;
         if (kind == K_ROOT) {
             for (int t = lane; t < nw; t += 64) L.dom[t] = I.dom0[t];
         } else {
@@ -2679,12 +2925,25 @@ __global__ __launch_bounds__(512, WM <= 2 ? CUBICS_LB_WAVES : 1) void search_ker
         }
         if (!uni(skip)) {
             if (VAR)
-                run_task_var<WM>(P, I, ctl, b, kind, F0, L, trail, C, lane, t_start);
+                run_task_var<WM>(P, I, ctl, b, kind, F0, T, L, trail, C, lane, t_start, &wgp);
             else
-                run_task<WM, FEAT, GLOB, SEGC, !TL>(P, I, ctl, b, kind, F0, L, trail, C, lane, t_start, LP, VP);
+                run_task<WM, FEAT, GLOB, SEGC, !TL>(P, I, ctl, b, kind, F0, T, L, trail, C, lane, t_start, &wgp, LP, VP);
         }
         C.tasks += 1;
-        flush<WM>(ctl, C, lane);
+        fold_var(C);
+        if (I.max_nodes) {  // the budget counts every node at the task's end
+            flush<WM>(ctl, C, lane);
+            held = -1;
+        }
+        T.rank = 0;
+        T.size = 1;
+        if (team) {
+            // the workgroup's last wave ends its share of the team's start
+            team = false;
+            uint32_t left = 0u;
+            if (lane == 0) left = __hip_atomic_fetch_sub(&team_left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (uniu(left) != 1u) continue;
+        }
         if (P.nrings > 1) {
             // the instance's last task ended: admit the next instance into
             // this ring (counted as pending before this task's end is)
@@ -2701,6 +2960,7 @@ __global__ __launch_bounds__(512, WM <= 2 ? CUBICS_LB_WAVES : 1) void search_ker
         }
         if (lane == 0) add_i(&P.g->pending, -1);
     }
+    if (held >= 0) flush<WM>(P.ctl + held, C, lane);
     if (lane == 0 && idle) add_u(&P.q->signal, 0xFFFFFFFFu);
 }
 
@@ -2736,7 +2996,9 @@ __global__ void value_features_kernel(const InstDev *inst, const uint32_t *dom, 
 __global__ void init_kernel(SearchParams P) {
     const uint32_t cells = P.qmask + 1u;
     const uint32_t R = (uint32_t)P.nrings;
-    const uint32_t seeded = R == 1u ? (uint32_t)P.B : min((uint32_t)P.B, R * (uint32_t)P.seeded);
+    const uint32_t started = R == 1u ? (uint32_t)P.B : min((uint32_t)P.B, R * (uint32_t)P.seeded);
+    // a team starts its instance without a queued ROOT task
+    const uint32_t seeded = P.team ? 0u : started;
     const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
     const uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t c = tid; c < R * cells; c += stride) {
@@ -2760,6 +3022,12 @@ __global__ void init_kernel(SearchParams P) {
         z.count = z.n_slots = z.nodes = z.fails = z.revisions = z.alg_bytes = z.steals = z.tasks = 0;
         z.done = z.reason = z.found = 0;
         z.live = b < seeded ? 1 : 0;
+        if (P.team && b < started) {
+            // the workgroups that start it (see the kernel's team set-up)
+            const uint32_t ring = b % R, slots = (started - ring + R - 1u) / R;
+            const uint32_t nb = ((uint32_t)P.nblocks - ring + R - 1u) / R;
+            z.live = (int32_t)((nb - b / R + slots - 1u) / slots);
+        }
         P.ctl[b] = z;
     }
     if (tid == 0 && P.trace_count) *P.trace_count = 0ull;
@@ -2769,11 +3037,11 @@ __global__ void init_kernel(SearchParams P) {
         P.qb->ring[tid].signal = 0u;
     }
     if (tid == 0) {
-        P.g->pending = (int32_t)seeded;
+        P.g->pending = P.team ? P.nblocks : (int32_t)seeded;
         P.g->produced = 0;
         P.g->stop = 0;
         P.g->stop_reason = 0;
-        P.g->next_inst = seeded;
+        P.g->next_inst = started;
     }
 }
 
@@ -2782,7 +3050,9 @@ __global__ void init_kernel(SearchParams P) {
 // Root fixpoint of one instance (one wave): writes the domains and the verdict.
 template <int WM>
 __global__ void root_kernel(SearchParams P, uint32_t *out, int32_t *failed, unsigned long long *revs) {
-    extern __shared__ uint32_t lds_raw[];
+    // 16-byte alignment: the words behind hold 64-bit sets that lanes update
+    // with 64-bit atomics, and the tables are staged by 16-byte stores
+    extern __shared__ __align__(16) uint32_t lds_raw[];
     const int lane = lane_id();
     const InstDev I = P.inst[0];
     Lds L;
