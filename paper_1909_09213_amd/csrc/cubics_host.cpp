@@ -89,6 +89,7 @@ struct cubics_ctx {
     int cu_count = 0;
     int wall_khz = 100000;
     int lds_max = 64 * 1024;  // LDS bytes one workgroup may allocate (160 KiB on gfx950)
+    size_t lds_cu = 160 * 1024;  // LDS bytes of a CU
     DevBuf inst, ctl, q, qseq, qdata, trail, rootout, tracecnt;
     DevBuf lnsdom, lnssol;  // large-neighbourhood search: initial domains, solutions
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -137,6 +138,7 @@ extern "C" int cubics_create(int32_t device, void *hip_stream, cubics_ctx **out)
     }
     c->cu_count = prop.multiProcessorCount;
     if (prop.sharedMemPerBlock >= 64 * 1024) c->lds_max = (int)prop.sharedMemPerBlock;
+    if (prop.maxSharedMemoryPerMultiProcessor >= 64 * 1024) c->lds_cu = prop.maxSharedMemoryPerMultiProcessor;
     int khz = 0;
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0)
         c->wall_khz = khz;
@@ -762,6 +764,7 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
     // ---- workers: fill the device with co-resident wavefronts.  A single
     // instance whose packed tables fit is staged in LDS once per workgroup;
     // the register-resident VAR path uses 8 workers per workgroup to share it.
+    const size_t LDS_STATIC_MAX = 48, LDS_GRANULE = 1280;  // the kernel's static words; LDS allocation unit
     const size_t LDS_WG_MAX = (size_t)ctx->lds_max - 256;  // the kernel keeps a few static words
     const bool vorder = L0.value_policy != nullptr;
     if (vorder && G.wmax > 2)
@@ -790,6 +793,13 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
     if (lds > LDS_WG_MAX) return fail(CUBICS_EUNSUPPORTED, "instance needs %zu bytes of LDS per worker", per_wave);
     int bpc = 0;
     HIPCHK(search_occupancy(G.wmax, &bpc, wpb, lds, tl, variant));
+    // LDS is handed out in blocks of 1280 bytes, which the query does not round
+    // up to: just below a boundary it counts a workgroup more per CU than fits
+    // (at 27,200 and 32,400 bytes 6 and 5 where 5 and 4 are resident)
+    if (lds > 0) {
+        const size_t held = (lds + LDS_STATIC_MAX + LDS_GRANULE - 1) / LDS_GRANULE * LDS_GRANULE;
+        bpc = std::min(bpc, (int)std::max<size_t>(1, ctx->lds_cu / held));
+    }
     if (bpc < 1) bpc = 1;
     int div = 1;
     // instances active per XCD ring: the caller's, else (0) the autotuned

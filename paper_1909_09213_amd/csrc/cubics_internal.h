@@ -96,6 +96,7 @@ struct QCtl {
     // idle workers of the ring (bits 0..23) | SIG_DONE | SIG_STOP: the one
     // word a busy worker polls; the rest is read only when it is non-zero
     uint32_t signal; int32_t _p3[31];
+    uint32_t groups; uint32_t _p4[31];  // groups of a team's start claimed so far
 };
 // Launch-wide control.
 struct QGlobal {

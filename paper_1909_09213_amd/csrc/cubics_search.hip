@@ -1422,6 +1422,14 @@ constexpr int DONATE_LEVELS = 2;
 constexpr int BACKOFF_MAX = 8;
 
 DEV uint32_t clk() { return (uint32_t)clock64(); }
+// Have `span` clocks passed between `then` and `now`?  32-bit clocks wrap
+// every 1.8 s and a workgroup may be idle for longer, so any distance counts
+// as passed except a `then` just ahead of `now` (another wave of the
+// workgroup read its clock later and stored it first).
+DEV bool clk_due(uint32_t now, uint32_t then, uint32_t span) {
+    const uint32_t d = now - then;
+    return d >= span && d < 0xFFF00000u;
+}
 
 struct WgPoll {  // in LDS, one per workgroup
     uint32_t time, slow;  // clock of the last refresh, of the last slow check
@@ -1433,7 +1441,7 @@ struct WgPoll {  // in LDS, one per workgroup
 DEV uint32_t wg_poll(const SearchParams &P, WgPoll *w, uint32_t now, long long t_start, int lane, uint32_t *odds) {
     uint32_t sig = 0u, od = 0u;
     if (lane == 0) {
-        if ((int)(now - lds_ld(&w->time)) >= (int)POLL_CLK) {
+        if (clk_due(now, lds_ld(&w->time), POLL_CLK)) {
             lds_st(&w->time, now);
             sig = ld_rlx(&P.q->signal);
             const int idle = (int)(sig & SIG_IDLE_MASK);
@@ -1443,7 +1451,7 @@ DEV uint32_t wg_poll(const SearchParams &P, WgPoll *w, uint32_t now, long long t
                 const int busy = P.ring_workers - idle;
                 if (want > 0) od = want >= busy ? 65536u : (uint32_t)(((long long)want << 16) / busy);
             }
-            if ((P.time_ticks || P.cancel) && (int)(now - lds_ld(&w->slow)) >= (int)SLOW_CLK) {
+            if ((P.time_ticks || P.cancel) && clk_due(now, lds_ld(&w->slow), SLOW_CLK)) {
                 lds_st(&w->slow, now);
                 int st = 0;
                 if (P.time_ticks && (long long)wall_clock64() - t_start > P.time_ticks) st = 2;
@@ -2697,17 +2705,22 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
     // idle_token: 1 while one idle wave of this workgroup polls the global
     // queue; drained: set once that wave saw no task pending anywhere
     __shared__ uint32_t idle_token, drained;
-    // team_left: this workgroup's waves that still work on their share of a
-    // team's start (the workgroup's share counts as one pending task)
-    __shared__ uint32_t team_left;
+    // A team's start is claimed in groups of shares, one share per wave of a
+    // full workgroup; a group counts as one pending task.  group: the one this
+    // workgroup claimed; team_left: its waves still working on it.
+    __shared__ uint32_t team_left, group;
     __shared__ WgPoll wgp;
     // (uni(): keeps what is derived from the launch shape in scalar registers)
     const int bid = uni((int)blockIdx.x), wpb = uni((int)(blockDim.x >> 6));
     const int wg_waves = min(P.nworkers - bid * wpb, wpb);
+    // the workgroup's ring (with one ring per XCD, workgroup b runs on XCD
+    // b % 8, as the hardware deals workgroups out in turn)
+    const int ring = P.nrings > 1 ? uni(bid % P.nrings) : 0;
     if (threadIdx.x == 0) {
         idle_token = 0u;
         drained = 0u;
         team_left = (uint32_t)wg_waves;
+        if (P.team) group = add_u(&P.qb->ring[ring].groups, 1u);
         wgp.time = wgp.slow = clk();
         wgp.sig = wgp.odds = 0u;
     }
@@ -2783,9 +2796,6 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
     }
     L.scr = base + off;  // the rest of the worker's words
     uint32_t *trail = P.trail + (size_t)wid * P.trail_words;
-    // the workgroup's ring (with one ring per XCD, workgroup b runs on XCD
-    // b % 8, as the hardware deals workgroups out in turn)
-    const int ring = P.nrings > 1 ? uni(bid % P.nrings) : 0;
     P.q = &P.qb->ring[ring];
     P.qseq += (size_t)ring * (P.qmask + 1u);
     P.qdata += (size_t)ring * (P.qmask + 1u) * P.slot_words;
@@ -2803,24 +2813,28 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
     // Without donation, eager split and admission no task is ever queued after
     // the launch: an idle wave whose ticket lies past the last one can leave.
     const bool fixed_tasks = !P.donate && P.split_target == 0 && P.nrings == 1;
-    // A team's start (P.team): the workgroups of a ring are dealt to its
-    // first instances, and every wave of them takes its share.
+    // A team's start (P.team): a ring's groups of shares are dealt to its first
+    // instances.  A workgroup claims one group as it starts and its waves take
+    // a share each; an idle wave claims the groups of workgroups that have not
+    // started (a grid need not be resident as a whole: the search must not
+    // wait for workgroups that wait for it to end).
     Team T = {0, 1};
-    bool team = false;
+    int share = wpb, share_step = 1, share_inst = -1, share_base = 0, share_size = 1;
+    bool sharing = false, wg_group = false, groups_open = P.team != 0;
+    int slots = 1, ngroups = 0;
     if (P.team) {
         const int R = P.nrings;
-        const int slots = uni(P.B > ring ? min(P.seeded, (P.B - ring + R - 1) / R) : 0);
-        const int nb = uni((P.nblocks - ring + R - 1) / R), jb = uni(bid / R);
-        if (slots > 0) {
-            const int slot = uni(jb % slots);
-            const int blocks = uni((nb - slot + slots - 1) / slots);
-            // the grid's last workgroup may hold fewer workers
-            const int last = P.nblocks - 1;
-            const int miss = uni(last % R == ring && (last / R) % slots == slot ? P.nblocks * wpb - P.nworkers : 0);
-            T.rank = uni(jb / slots) * wpb + wave;
-            T.size = blocks * wpb - miss;
-            direct = slot * R + ring;
-            team = true;
+        slots = uni(min(P.seeded, (P.B - ring + R - 1) / R));
+        ngroups = uni((P.nblocks - ring + R - 1) / R);
+        const int g = (int)uniu(group);
+        if (g < ngroups) {
+            const int slot = uni(g % slots);
+            share_inst = slot * P.nrings + ring;
+            share_base = uni(g / slots) * wpb;
+            share_size = uni((ngroups - slot + slots - 1) / slots) * wpb;
+            share = wave;
+            share_step = wg_waves;  // the last workgroup may hold fewer waves
+            wg_group = sharing = true;
         }
     }
     // Idle waves: only the one holding its workgroup's token takes a ticket
@@ -2840,7 +2854,12 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
         F0.x = F0.depth = F0.side = 0;
 #pragma unroll
         for (int k = 0; k < WM; ++k) F0.v[k] = 0u;
-        if (direct >= 0) {
+        if (share < wpb) {
+            b = share_inst;
+            T.rank = share_base + share;
+            T.size = share_size;
+            share += share_step;
+        } else if (direct >= 0) {
             b = direct;
             direct = -1;
         } else {
@@ -2852,6 +2871,30 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
                 if (poller) backoff = 1;
             }
             if (poller) {
+                if (groups_open) {
+                    // no ticket is taken before every group is claimed
+                    uint32_t g = 0u;
+                    if (lane == 0) {
+                        g = ld_rlx(&P.q->groups);
+                        if (g < (uint32_t)ngroups) g = add_u(&P.q->groups, 1u);
+                    }
+                    const int gi = (int)uniu(g);
+                    if (gi < ngroups) {
+                        const int slot = uni(gi % slots);
+                        share_inst = slot * P.nrings + ring;
+                        share_base = uni(gi / slots) * wpb;
+                        share_size = uni((ngroups - slot + slots - 1) / slots) * wpb;
+                        share = 0;
+                        share_step = 1;
+                        sharing = true;
+                        if (lane == 0) lds_st(&idle_token, 0u);
+                        poller = 0;
+                        if (idle && lane == 0) add_u(&P.q->signal, 0xFFFFFFFFu);  // idle - 1
+                        idle = false;
+                        continue;
+                    }
+                    groups_open = false;
+                }
                 if (!have_ticket) {
                     if (lane == 0) ticket = add_u(&P.q->head, 1u);
                     ticket = uniu(ticket);
@@ -2937,12 +2980,17 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
         }
         T.rank = 0;
         T.size = 1;
-        if (team) {
-            // the workgroup's last wave ends its share of the team's start
-            team = false;
-            uint32_t left = 0u;
-            if (lane == 0) left = __hip_atomic_fetch_sub(&team_left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (uniu(left) != 1u) continue;
+        if (sharing) {
+            // a group ends with its last share; a workgroup's group with the
+            // last of its waves
+            if (share < wpb) continue;
+            sharing = false;
+            if (wg_group) {
+                wg_group = false;
+                uint32_t left = 0u;
+                if (lane == 0) left = __hip_atomic_fetch_sub(&team_left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (uniu(left) != 1u) continue;
+            }
         }
         if (P.nrings > 1) {
             // the instance's last task ended: admit the next instance into
@@ -3023,7 +3071,7 @@ __global__ void init_kernel(SearchParams P) {
         z.done = z.reason = z.found = 0;
         z.live = b < seeded ? 1 : 0;
         if (P.team && b < started) {
-            // the workgroups that start it (see the kernel's team set-up)
+            // the groups of its team (see the kernel's team set-up)
             const uint32_t ring = b % R, slots = (started - ring + R - 1u) / R;
             const uint32_t nb = ((uint32_t)P.nblocks - ring + R - 1u) / R;
             z.live = (int32_t)((nb - b / R + slots - 1u) / slots);
@@ -3035,6 +3083,7 @@ __global__ void init_kernel(SearchParams P) {
         P.qb->ring[tid].head = 0;
         P.qb->ring[tid].tail = seeded > tid ? (seeded - tid + R - 1u) / R : 0u;
         P.qb->ring[tid].signal = 0u;
+        P.qb->ring[tid].groups = 0u;
     }
     if (tid == 0) {
         P.g->pending = P.team ? P.nblocks : (int32_t)seeded;

@@ -82,3 +82,18 @@ def test_worker_bound_searches_leave_when_nothing_is_queued(ctx, cb):
             assert (r.verdict, r.nodes) == ("SAT" if ref.count else "UNSAT", ref.nodes)
             if r.solutions is not None and len(r.solutions):
                 assert oracle.verify(x, np.asarray(r.solutions[0]))
+
+
+@pytest.mark.parametrize("batch", [1, 5, 40])
+def test_more_workers_than_fit_on_the_device(ctx, cb, batch):
+    """A grid that is not resident as a whole: workgroups that start late (or
+    find their share taken) must not be waited for."""
+    insts = [cspgen.rb_sweep(i, base=703, nlo=8, nhi=11, dlo=4, dhi=6, plo=350, phi=550, tlo=300, thi=450)
+             for i in range(batch)]
+    probs = [ctx.load(x) for x in insts]
+    for layout, active in ((1, 0), (3, 0), (1, 2)):
+        print("late", batch, layout, active, flush=True)
+        res = ctx.solve_batch(probs, cb.MODE_COUNT, workers=30001, layout=layout, active_per_xcd=active)
+        for x, r in zip(insts, res):
+            ref = oracle.solve(x, oracle.MODE_COUNT)
+            assert (r.count, r.nodes, r.fails) == (ref.count, ref.nodes, ref.fails)
