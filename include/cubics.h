@@ -251,7 +251,7 @@ int cubics_root(cubics_prob *prob, int32_t layout, uint32_t *out_bits, int32_t *
    error.  Workers check them periodically: max_nodes every 128 nodes of a
    worker, so a search may run up to 128 nodes per worker past it; a stop
    (time_ms, cancel, another worker's find-first solution) is seen about
-   every 20 us of a worker's own time, at its next node (the register layout:
+   every 100 us of a worker's own time, at its next node (the register layout:
    within 16 nodes), the clock and the cancel flag about every millisecond.
    `limits` may be NULL (no limits, defaults). */
 int cubics_solve(cubics_prob *prob, int32_t mode, const cubics_limits *limits,

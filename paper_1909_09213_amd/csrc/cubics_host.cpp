@@ -90,7 +90,7 @@ struct cubics_ctx {
     int wall_khz = 100000;
     int lds_max = 64 * 1024;  // LDS bytes one workgroup may allocate (160 KiB on gfx950)
     size_t lds_cu = 160 * 1024;  // LDS bytes of a CU
-    DevBuf inst, ctl, q, qseq, qdata, trail, rootout, tracecnt;
+    DevBuf inst, ctl, q, qdata, trail, rootout, tracecnt;
     DevBuf lnsdom, lnssol;  // large-neighbourhood search: initial domains, solutions
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     int32_t *cancel_host = nullptr;  // pinned, polled by the kernel
@@ -155,7 +155,7 @@ extern "C" int cubics_create(int32_t device, void *hip_stream, cubics_ctx **out)
 extern "C" void cubics_destroy(cubics_ctx *c) {
     if (!c) return;
     (void)hipSetDevice(c->device);
-    c->inst.release(); c->ctl.release(); c->q.release(); c->qseq.release();
+    c->inst.release(); c->ctl.release(); c->q.release(); 
     c->qdata.release(); c->trail.release(); c->rootout.release(); c->tracecnt.release();
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
@@ -764,7 +764,7 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
     // ---- workers: fill the device with co-resident wavefronts.  A single
     // instance whose packed tables fit is staged in LDS once per workgroup;
     // the register-resident VAR path uses 8 workers per workgroup to share it.
-    const size_t LDS_STATIC_MAX = 48, LDS_GRANULE = 1280;  // the kernel's static words; LDS allocation unit
+    const size_t LDS_STATIC_MAX = 128, LDS_GRANULE = 1280;  // the kernel's static words; LDS allocation unit
     const size_t LDS_WG_MAX = (size_t)ctx->lds_max - 256;  // the kernel keeps a few static words
     const bool vorder = L0.value_policy != nullptr;
     if (vorder && G.wmax > 2)
@@ -849,7 +849,7 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
     const auto static_bytes = [&](int nw_) {
         const size_t c = (size_t)queue_cells(nw_) * ring_count(nw_);
         return al(sizeof(InstDev) * (size_t)B) + al(sizeof(InstCtl) * (size_t)B) + al(sizeof(QBlock)) +
-               al(4ull * c) + al(4ull * c * slot_words) + 4ull * trail_words * (size_t)nw_;
+               al(4ull * c * slot_words) + 4ull * trail_words * (size_t)nw_;
     };
     if (static_scratch) {
         if (static_bytes(1) > CUBICS_STATIC_SCRATCH_BYTES)
@@ -868,7 +868,7 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
     const uint32_t cap = queue_cells(nworkers);  // per ring
     const int nrings = ring_count(nworkers);
     const size_t cells = (size_t)cap * nrings;
-    void *d_inst, *d_ctl, *d_q, *d_qseq, *d_qdata, *d_trail;
+    void *d_inst, *d_ctl, *d_q, *d_qdata, *d_trail;
     int rc;
     if (static_scratch) {
         uint8_t *base = nullptr;
@@ -882,20 +882,17 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
         d_inst = take(sizeof(InstDev) * (size_t)B);
         d_ctl = take(sizeof(InstCtl) * (size_t)B);
         d_q = take(sizeof(QBlock));
-        d_qseq = take(4ull * cells);
         d_qdata = take(4ull * cells * slot_words);
         d_trail = take(4ull * trail_words * (size_t)nworkers);
     } else {
         if ((rc = ctx->inst.ensure(sizeof(InstDev) * (size_t)B))) return rc;
         if ((rc = ctx->ctl.ensure(sizeof(InstCtl) * (size_t)B))) return rc;
         if ((rc = ctx->q.ensure(sizeof(QBlock)))) return rc;
-        if ((rc = ctx->qseq.ensure(4ull * cells))) return rc;
         if ((rc = ctx->qdata.ensure(4ull * cells * slot_words))) return rc;
         if ((rc = ctx->trail.ensure(4ull * trail_words * (size_t)nworkers))) return rc;
         d_inst = ctx->inst.p;
         d_ctl = ctx->ctl.p;
         d_q = ctx->q.p;
-        d_qseq = ctx->qseq.p;
         d_qdata = ctx->qdata.p;
         d_trail = ctx->trail.p;
     }
@@ -926,8 +923,7 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
     P.g = &P.qb->g;
     P.nrings = nrings;
     P.seeded = nrings > 1 ? gang : B;
-    P.qseq = (uint32_t *)d_qseq;
-    P.qdata = (uint32_t *)d_qdata;
+    P.qdata0 = P.qdata = (uint32_t *)d_qdata;
     P.qmask = cap - 1;
     P.slot_words = slot_words;
     P.trail = (uint32_t *)d_trail;

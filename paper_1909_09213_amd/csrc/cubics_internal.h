@@ -110,9 +110,18 @@ struct QGlobal {
 // ring holding a few instances at a time, so that the tables one XCD's
 // workers read stay in that XCD's L2.
 constexpr int MAX_RINGS = 8;
+// Copies of the rings' signal words that busy workgroups read in their place
+// (workgroup b reads copy b % QVIEWS, always of its own ring): the wall clock
+// of the copy's last refresh in the upper half, the word in the lower.
+constexpr int QVIEWS = 32;
+static_assert(QVIEWS % MAX_RINGS == 0, "a copy belongs to one ring");
+struct QView {
+    unsigned long long word; unsigned long long _p[15];
+};
 struct QBlock {
     QGlobal g;
     QCtl ring[MAX_RINGS];
+    QView view[QVIEWS];
 };
 
 constexpr uint32_t SIG_IDLE_MASK = 0x00FFFFFFu;
@@ -120,7 +129,11 @@ constexpr uint32_t SIG_DONE = 1u << 29;  // some instance's done flag is set
 constexpr uint32_t SIG_STOP = 1u << 30;  // the whole launch stops
 
 // Queue slot / trail frame header layout (uint32 words).
-constexpr int SLOT_HDR = 16;   // [0] inst [1] kind [2] x [3] depth [4..12) vals [12] side
+constexpr int SLOT_HDR = 16;   // [0] inst [1] kind [2] x [3] depth [4..12) vals [12] side [15] sequence
+// The cell's sequence number lies in its slot: every waiting wave polls a line
+// of its own.  (In an array of words, the cells that a thousand idle
+// workgroups poll shared a few lines of one memory channel.)
+constexpr int SLOT_SEQ = 15;
 constexpr int FRAME_HDR = 32;  // [0] x [1] depth [2] flags [3] side [4..12) vals [16..21) features [24..26) node stamp
 
 // Learned policy (device).  Parameter vector theta (fp32 master copy):
@@ -153,10 +166,11 @@ struct SearchParams {
     QBlock *qb;
     QCtl *q;             // the worker's ring (the kernel points it at ring b % nrings)
     QGlobal *g;
+    unsigned long long *view;  // the workgroup's copy of its ring's signal word (set by the kernel)
     int32_t nrings;      // 1, or MAX_RINGS with admission of instances per ring
     int32_t seeded;      // instances queued per ring at launch (rings > 1)
-    uint32_t *qseq;      // [nrings][qmask + 1] (the kernel offsets it per ring)
-    uint32_t *qdata;     // [nrings][qmask + 1][slot_words]
+    uint32_t *qdata0;    // [nrings][qmask + 1][slot_words], every ring's cells
+    uint32_t *qdata;     // the worker's ring's (set by the kernel)
     uint32_t qmask;      // cells per ring - 1
     uint32_t slot_words;
     uint32_t *trail;

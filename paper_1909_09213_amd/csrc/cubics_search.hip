@@ -109,6 +109,7 @@ DEV uint32_t add_u(uint32_t *p, uint32_t v) {
 DEV uint32_t or_u(uint32_t *p, uint32_t v) {
     return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+DEV void st_rlx_u64(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 DEV void st_rlx(uint32_t *p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -137,9 +138,10 @@ DEV bool cas_u32(uint32_t *p, uint32_t *expected, uint32_t desired) {
 // workgroup-scope words in LDS (the idle-poll token)
 DEV bool lds_take(uint32_t *p) {
     uint32_t e = 0u;
-    return __hip_atomic_compare_exchange_strong(p, &e, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+    return __hip_atomic_compare_exchange_strong(p, &e, 1u, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+DEV void lds_give(uint32_t *p) { __hip_atomic_store(p, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP); }
 DEV uint32_t lds_ld(uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 DEV void lds_st(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 DEV bool cas_i(int32_t *p, int expected, int desired) {
@@ -1216,6 +1218,32 @@ DEV void stop_launch(const SearchParams &P, int reason) {
     signal_rings(P, SIG_STOP);
 }
 
+// No task is pending anywhere any more: tell the waves that wait on a cell
+// (tickets taken beyond the tail).  A wave that takes its ticket after the
+// head is read here reads the pending count after that, and finds it zero.
+constexpr uint32_t SEQ_CLOSED = 0x40000000u;  // cell sequence of ticket t: t + SEQ_CLOSED
+DEV void close_rings(const SearchParams &P, int lane) {
+    const uint32_t cells = P.qmask + 1u;
+    for (int r = 0; r < P.nrings; ++r) {
+        QCtl *q = &P.qb->ring[r];
+        uint32_t *data = P.qdata0 + (size_t)r * cells * P.slot_words;
+        uint32_t head = 0u, tail = 0u;
+        if (lane == 0) {
+            head = ld_rlx(&q->head);
+            tail = ld_rlx(&q->tail);
+        }
+        head = uniu(head);
+        tail = uniu(tail);
+        const int waiting = (int)(head - tail);
+        for (int t = lane; t < waiting; t += 64) {
+            const uint32_t pos = tail + (uint32_t)t;
+            st_rlx(data + (size_t)(pos & P.qmask) * P.slot_words + SLOT_SEQ, pos + SEQ_CLOSED);
+        }
+    }
+}
+
+DEV uint32_t *slot_of(const SearchParams &P, uint32_t cell) { return P.qdata + (size_t)cell * P.slot_words; }
+
 // Reserve the next position: one fetch-add on the tail.  (A compare-and-swap
 // made the donors of a search's tail race for the same word.)  Refused while
 // half of the cells are waiting to be claimed; the host sizes a ring for at
@@ -1223,12 +1251,14 @@ DEV void stop_launch(const SearchParams &P, int reason) {
 // that check at once, and the cell's previous position is always one whose
 // ticket was taken: its consumer copies the slot and hands the cell back
 // without waiting for anyone, so the wait below ends.
-DEV bool q_reserve(const SearchParams &P, uint32_t *cell, uint32_t *posout) {
+// A donor (share > 0) is refused too while `share` tasks wait unclaimed.
+DEV bool q_reserve(const SearchParams &P, int share, uint32_t *cell, uint32_t *posout) {
     const uint32_t tail = ld_rlx(&P.q->tail), head = ld_rlx(&P.q->head);
-    if ((int)(tail - head) >= (int)((P.qmask + 1u) >> 1)) return false;
+    const int waiting = (int)(tail - head);
+    if (waiting >= (int)((P.qmask + 1u) >> 1) || (share > 0 && waiting >= share)) return false;
     const uint32_t pos = add_u(&P.q->tail, 1u);
     const uint32_t c = pos & P.qmask;
-    while (ld_rlx(&P.qseq[c]) != pos) __builtin_amdgcn_s_sleep(1);
+    while (ld_rlx(slot_of(P, c) + SLOT_SEQ) != pos) __builtin_amdgcn_s_sleep(1);
     slot_claimed();
     *cell = c;
     *posout = pos;
@@ -1239,11 +1269,11 @@ DEV bool q_reserve(const SearchParams &P, uint32_t *cell, uint32_t *posout) {
 // parent snapshot snap, which is nw words in LDS or global memory).
 template <int WM>
 DEV bool push_frame(const SearchParams &P, int inst, int x, int depth, const uint32_t (&vals)[WM],
-                    const uint32_t *snap, int nw, int lane, int side = 0) {
+                    const uint32_t *snap, int nw, int lane, int side = 0, int share = 0) {
     uint32_t cell = 0, pos = 0;
     int ok = 0;
     if (lane == 0) {
-        ok = q_reserve(P, &cell, &pos) ? 1 : 0;
+        ok = q_reserve(P, share, &cell, &pos) ? 1 : 0;
         // counted as pending, and among its instance's live tasks, before it
         // is published (this task is still pending itself)
         if (ok) {
@@ -1255,8 +1285,8 @@ DEV bool push_frame(const SearchParams &P, int inst, int x, int depth, const uin
     if (!ok) return false;
     cell = uniu(cell);
     pos = uniu(pos);
-    uint32_t *s = P.qdata + (size_t)cell * P.slot_words;
-    if (lane < SLOT_HDR) {  // header word `lane`
+    uint32_t *s = slot_of(P, cell);
+    if (lane < SLOT_SEQ) {  // header word `lane`
         uint32_t h = 0u;
         if (lane == 0) h = (uint32_t)inst;
         if (lane == 1) h = (uint32_t)K_FRAME;
@@ -1270,7 +1300,7 @@ DEV bool push_frame(const SearchParams &P, int inst, int x, int depth, const uin
     }
     for (int t = lane; t < nw; t += 64) st_rlx(s + SLOT_HDR + t, snap[t]);
     slot_stores_done();
-    if (lane == 0) st_rlx(&P.qseq[cell], pos + 1u);
+    if (lane == 0) st_rlx(s + SLOT_SEQ, pos + 1u);
     return true;
 }
 
@@ -1375,34 +1405,55 @@ DEV void fold_var(Counters &C) {
     C.vrev = C.vchg = C.vpop = 0u;
 }
 
-template <int WM>
-DEV void flush(InstCtl *ctl, Counters &C, int lane) {
+// The counters of one instance (InstCtl's), summed by the waves of a
+// workgroup in LDS; the last wave to leave adds them to the control block.
+// Atomics on one line are served one after another, about 5 ns each: adding
+// them wave by wave made an 8-queens launch 46 ns longer per worker.
+struct WgSum {
+    u64 nodes, fails, count, steals, tasks, revisions, alg_bytes;
+};
+
+// Add C to an instance's counters: InstCtl in global memory or WgSum in LDS.
+template <int SCOPE, class T>
+DEV void flush_to(T *ctl, Counters &C, u64 rev, u64 bytes) {
+    const auto add = [](auto *p, u64 v) {
+        if (v) __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, SCOPE);
+    };
+    add(&ctl->nodes, C.nodes);
+    add(&ctl->fails, C.fails);
+    add(&ctl->count, C.sols);
+    add(&ctl->steals, C.steals);
+    add(&ctl->tasks, C.tasks);
+    add(&ctl->revisions, rev);
+    add(&ctl->alg_bytes, bytes);
+}
+DEV void flush(InstCtl *ctl, WgSum *sum, Counters &C, int lane) {
     fold_var(C);
     const u64 rev = wave_sumu64(C.rev), bytes = wave_sumu64(C.bytes) + C.ubytes;
     if (lane == 0) {
-        if (C.nodes) add_u64(&ctl->nodes, C.nodes);
-        if (C.fails) add_u64(&ctl->fails, C.fails);
-        if (C.sols) add_u64(&ctl->count, C.sols);
-        if (C.steals) add_u64(&ctl->steals, C.steals);
-        if (C.tasks) add_u64(&ctl->tasks, C.tasks);
-        if (rev) add_u64(&ctl->revisions, rev);
-        if (bytes) add_u64(&ctl->alg_bytes, bytes);
+        if (sum) flush_to<__HIP_MEMORY_SCOPE_WORKGROUP>(sum, C, rev, bytes);
+        else flush_to<__HIP_MEMORY_SCOPE_AGENT>(ctl, C, rev, bytes);
     }
     C.nodes = C.fails = C.sols = C.steals = C.tasks = 0;
     C.rev = C.bytes = C.ubytes = 0;
 }
 
-// Busy workers look at their ring every POLL_CLK core clocks (about 20 us):
+// Busy workers look at their ring every POLL_CLK core clocks (about 80 us):
 // the first wave of a workgroup to find the workgroup's view older than that
-// reads the ring's words, the others use its view in LDS, so that thousands
-// of waves do not load one word at a time.  The view holds the stop flags and
-// the odds (of 65536) with which a busy wave should donate: the tasks wanted
-// (idle waves beyond the queued tasks) over the busy waves, so that a few
-// idle waves do not make every busy one give work away.
+// reads the ring's signal word, the others use its view in LDS, and of the
+// workgroups that share one of QVIEWS copies in memory only the one that finds
+// the copy VIEW_TICKS old reads the word itself: one address answers some
+// 10^8 loads a second, and 1,280 workgroups that read it every 20 us held up
+// every hand-over.  (768 labels on 5,120 workers: 17.7 ms without the copies,
+// 8.9 with them; with polls every 40 and 80 us 7.7 and 6.3 ms.)  The view holds the stop
+// flags and the odds (of 65536) with which a busy wave should donate: the idle
+// waves over the busy ones, so that a few idle waves do not make every busy
+// one give work away.
 // The host's cancel flag (a read over PCIe) and the time limit are looked at
 // every SLOW_CLK (about 1 ms).
-constexpr uint32_t POLL_CLK = 48000;
+constexpr uint32_t POLL_CLK = 192000;
 constexpr uint32_t SLOW_CLK = 2400000;
+constexpr uint32_t VIEW_TICKS = 2000;  // 20 us of the 100 MHz wall clock
 // The register layout, where a node takes one or two microseconds, looks at
 // the clock every VAR_CHECK nodes; the LDS layouts at every node.
 constexpr int VAR_CHECK = 16;
@@ -1419,7 +1470,7 @@ constexpr uint32_t ACCT_CLK = 120000;
 // hand-over (a few microseconds on either side).
 constexpr int DONATE_LEVELS = 2;
 // Longest back-off of an idle wave between two polls of its queue cell.
-constexpr int BACKOFF_MAX = 8;
+constexpr int BACKOFF_MAX = 16;
 
 DEV uint32_t clk() { return (uint32_t)clock64(); }
 // Have `span` clocks passed between `then` and `now`?  32-bit clocks wrap
@@ -1443,13 +1494,18 @@ DEV uint32_t wg_poll(const SearchParams &P, WgPoll *w, uint32_t now, long long t
     if (lane == 0) {
         if (clk_due(now, lds_ld(&w->time), POLL_CLK)) {
             lds_st(&w->time, now);
-            sig = ld_rlx(&P.q->signal);
+            const uint32_t t = (uint32_t)wall_clock64();
+            const u64 v = ld_rlx_u64(P.view);
+            sig = (uint32_t)v;
+            if (t - (uint32_t)(v >> 32) >= VIEW_TICKS) {
+                st_rlx_u64(P.view, ((u64)t << 32) | sig);  // others wait for this refresh
+                sig = ld_rlx(&P.q->signal);
+                st_rlx_u64(P.view, ((u64)t << 32) | sig);
+            }
             const int idle = (int)(sig & SIG_IDLE_MASK);
             if (P.donate && idle > 0) {
-                const int queued = (int)(ld_rlx(&P.q->tail) - ld_rlx(&P.q->head));
-                const int want = idle - (queued > 0 ? queued : 0);
                 const int busy = P.ring_workers - idle;
-                if (want > 0) od = want >= busy ? 65536u : (uint32_t)(((long long)want << 16) / busy);
+                od = idle >= busy ? 65536u : (uint32_t)(((long long)idle << 16) / busy);
             }
             if ((P.time_ticks || P.cancel) && clk_due(now, lds_ld(&w->slow), SLOW_CLK)) {
                 lds_st(&w->slow, now);
@@ -2186,7 +2242,7 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
 #pragma unroll
                     for (int k = 0; k < WM; ++k) keeps |= (D.v[k] & ~give[k]) != 0u;
                     if ((more || keeps) && deepest - D.depth >= levels &&
-                        push_frame<WM>(P, b, D.x, D.depth, give, f + FRAME_HDR, nw, lane, D.side)) {
+                        push_frame<WM>(P, b, D.x, D.depth, give, f + FRAME_HDR, nw, lane, D.side, (int)(sig & SIG_IDLE_MASK))) {
                         if (lane < WM) {
                             uint32_t v = 0u;
 #pragma unroll
@@ -2645,7 +2701,7 @@ DEV void run_task_var(const SearchParams &P, const InstDev &I, InstCtl *ctl, int
                         const uint32_t left = D.v[0] & ~g1[0];
                         D.v[0] = g1[0];
                         if ((more || left) && deepest - D.depth >= DONATE_LEVELS &&
-                            push_frame<WM>(P, b, D.x, D.depth, D.v, f + FRAME_HDR, n, lane, D.side)) {
+                            push_frame<WM>(P, b, D.x, D.depth, D.v, f + FRAME_HDR, n, lane, D.side, (int)(sig & SIG_IDLE_MASK))) {
                             if (tsel == sp - 1) F.v[0] = left;
                             else if (lane == tsel) mval = left;
                             C.steals += 1;
@@ -2709,6 +2765,13 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
     // full workgroup; a group counts as one pending task.  group: the one this
     // workgroup claimed; team_left: its waves still working on it.
     __shared__ uint32_t team_left, group;
+    // wg_sum: see WgSum; waves_left: waves that have not left the kernel
+    __shared__ WgSum wg_sum;
+    __shared__ uint32_t waves_left;
+    // wg_idle: the workgroup's idle waves; wg_told: how many of them the
+    // ring's signal word counts (kept by the holder of the idle token, so that
+    // a workgroup changes that word once for several of its waves)
+    __shared__ uint32_t wg_idle, wg_told;
     __shared__ WgPoll wgp;
     // (uni(): keeps what is derived from the launch shape in scalar registers)
     const int bid = uni((int)blockIdx.x), wpb = uni((int)(blockDim.x >> 6));
@@ -2721,6 +2784,9 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
         drained = 0u;
         team_left = (uint32_t)wg_waves;
         if (P.team) group = add_u(&P.qb->ring[ring].groups, 1u);
+        waves_left = (uint32_t)wg_waves;
+        wg_sum = WgSum{};
+        wg_idle = wg_told = 0u;
         wgp.time = wgp.slow = clk();
         wgp.sig = wgp.odds = 0u;
     }
@@ -2797,8 +2863,8 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
     L.scr = base + off;  // the rest of the worker's words
     uint32_t *trail = P.trail + (size_t)wid * P.trail_words;
     P.q = &P.qb->ring[ring];
-    P.qseq += (size_t)ring * (P.qmask + 1u);
-    P.qdata += (size_t)ring * (P.qmask + 1u) * P.slot_words;
+    P.view = &P.qb->view[bid % QVIEWS].word;  // QVIEWS is a multiple of the rings
+    P.qdata = P.qdata0 + (size_t)ring * (P.qmask + 1u) * P.slot_words;
     const long long t_start = (long long)wall_clock64();
     Counters C = {};
     bool idle = false;
@@ -2837,6 +2903,10 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
             wg_group = sharing = true;
         }
     }
+    // the instance summed in LDS: the one the workgroup starts with (a single
+    // instance's searches and team starts); not under a node budget, which
+    // counts every task's nodes at its end
+    const int sum_inst = P.B == 1 ? 0 : (wg_group ? share_inst : -1);
     // Idle waves: only the one holding its workgroup's token takes a ticket
     // and waits on its cell (backing off exponentially, up to BACKOFF_MAX
     // sleeps of 2048 clocks between polls); the others wait on the token in LDS.  A wave holding a ticket
@@ -2844,7 +2914,7 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
     // tells its workgroup through LDS.
     int backoff = 1;
     int poller = 0;  // wave-uniform: this wave holds the token
-    int have_ticket = 0, polls = 0;
+    int have_ticket = 0;
     uint32_t ticket = 0;
     for (;;) {
         uint32_t cell = 0, pos = 0;
@@ -2863,80 +2933,94 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
             b = direct;
             direct = -1;
         } else {
-            int got = 0, fin = 0;
+            if (!idle) {
+                if (lane == 0) __hip_atomic_fetch_add(&wg_idle, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                idle = true;
+            }
             if (!poller) {
                 int t = 0;
                 if (lane == 0) t = lds_take(&idle_token) ? 1 : 0;
                 poller = uni(t);
-                if (poller) backoff = 1;
-            }
-            if (poller) {
-                if (groups_open) {
-                    // no ticket is taken before every group is claimed
-                    uint32_t g = 0u;
-                    if (lane == 0) {
-                        g = ld_rlx(&P.q->groups);
-                        if (g < (uint32_t)ngroups) g = add_u(&P.q->groups, 1u);
-                    }
-                    const int gi = (int)uniu(g);
-                    if (gi < ngroups) {
-                        const int slot = uni(gi % slots);
-                        share_inst = slot * P.nrings + ring;
-                        share_base = uni(gi / slots) * wpb;
-                        share_size = uni((ngroups - slot + slots - 1) / slots) * wpb;
-                        share = 0;
-                        share_step = 1;
-                        sharing = true;
-                        if (lane == 0) lds_st(&idle_token, 0u);
-                        poller = 0;
-                        if (idle && lane == 0) add_u(&P.q->signal, 0xFFFFFFFFu);  // idle - 1
-                        idle = false;
-                        continue;
-                    }
-                    groups_open = false;
-                }
-                if (!have_ticket) {
-                    if (lane == 0) ticket = add_u(&P.q->head, 1u);
-                    ticket = uniu(ticket);
-                    have_ticket = 1;
-                    polls = 0;
-                }
-                if (lane == 0) {
-                    got = ld_rlx(&P.qseq[ticket & P.qmask]) == ticket + 1u;
-                    if (!got && (++polls & 1) == 0 &&
-                        (ld_rlx_i(&P.g->pending) == 0 || (fixed_tasks && (int)(ticket - ld_rlx(&P.q->tail)) >= 0))) {
-                        fin = 1;
-                        lds_st(&drained, 1u);
-                    }
-                }
-                got = uni(got);
-            } else if (lane == 0) {
-                fin = lds_ld(&drained) != 0u;
-            }
-            if (!got) {
-                if (lane == 0 && !idle) add_u(&P.q->signal, 1u);
-                idle = true;
-                if (uni(fin)) break;
-                if (poller) {
-                    for (int z = 0; z < backoff; ++z) __builtin_amdgcn_s_sleep(32);
-                    backoff = backoff < BACKOFF_MAX ? backoff * 2 : BACKOFF_MAX;
-                } else {
+                if (!poller) {
+                    int out = 0;
+                    if (lane == 0) out = (int)lds_ld(&drained);
+                    if (uni(out)) break;
                     __builtin_amdgcn_s_sleep(16);
+                    continue;
                 }
+                backoff = 1;
+            }
+            if (groups_open) {
+                // no ticket is taken before every group is claimed
+                uint32_t g = 0u;
+                if (lane == 0) {
+                    g = ld_rlx(&P.q->groups);
+                    if (g < (uint32_t)ngroups) g = add_u(&P.q->groups, 1u);
+                }
+                const int gi = (int)uniu(g);
+                if (gi < ngroups) {
+                    const int slot = uni(gi % slots);
+                    share_inst = slot * P.nrings + ring;
+                    share_base = uni(gi / slots) * wpb;
+                    share_size = uni((ngroups - slot + slots - 1) / slots) * wpb;
+                    share = 0;
+                    share_step = 1;
+                    sharing = true;
+                    poller = 0;
+                    idle = false;
+                    if (lane == 0) {
+                        __hip_atomic_fetch_sub(&wg_idle, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        lds_give(&idle_token);
+                    }
+                    continue;
+                }
+                groups_open = false;
+            }
+            // The end of the launch comes to a waiting wave through its cell
+            // (see close_rings); a wave that takes its ticket later finds no
+            // task pending.  So the word that counts them is read once per
+            // ticket, not by every waiting wave all the time.
+            int state = 0;  // 1 a task, 2 the end
+            if (lane == 0) {
+                int none = 0;
+                if (!have_ticket) {
+                    ticket = add_u(&P.q->head, 1u);
+                    slot_stores_done();  // the ticket is taken before the count is read
+                    none = ld_rlx_i(&P.g->pending) == 0 ||
+                           (fixed_tasks && (int)(ticket - ld_rlx(&P.q->tail)) >= 0);
+                }
+                const uint32_t seq = ld_rlx(slot_of(P, ticket & P.qmask) + SLOT_SEQ);
+                state = seq == ticket + 1u ? 1 : (none || seq == ticket + SEQ_CLOSED ? 2 : 0);
+                // tell the ring how many waves are idle here
+                const int now_idle = (int)lds_ld(&wg_idle) - (state == 1 ? 1 : 0), told = (int)lds_ld(&wg_told);
+                if (now_idle != told && state != 2) {
+                    add_u(&P.q->signal, (uint32_t)(now_idle - told));
+                    lds_st(&wg_told, (uint32_t)now_idle);
+                }
+            }
+            ticket = uniu(ticket);
+            have_ticket = 1;
+            state = uni(state);
+            if (state == 2) {
+                if (lane == 0) lds_st(&drained, 1u);
+                break;
+            }
+            if (state == 0) {
+                for (int z = 0; z < backoff; ++z) __builtin_amdgcn_s_sleep(32);
+                backoff = backoff < BACKOFF_MAX ? backoff * 2 : BACKOFF_MAX;
                 continue;
             }
             slot_claimed();
             pos = ticket;
             cell = ticket & P.qmask;
             have_ticket = 0;
-            if (lane == 0) lds_st(&idle_token, 0u);  // hand the token on
             poller = 0;
-            backoff = 1;
-            if (idle) {
-                if (lane == 0) add_u(&P.q->signal, 0xFFFFFFFFu);  // idle - 1
-                idle = false;
+            idle = false;
+            if (lane == 0) {  // hand the token on
+                __hip_atomic_fetch_sub(&wg_idle, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                lds_give(&idle_token);
             }
-            s = P.qdata + (size_t)cell * P.slot_words;
+            s = slot_of(P, cell);
             const uint32_t hw = lane < SLOT_HDR ? ld_rlx(s + lane) : 0u;  // header word `lane`
             b = __builtin_amdgcn_readlane((int)hw, 0);
             kind = __builtin_amdgcn_readlane((int)hw, 1);
@@ -2948,7 +3032,7 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
         }
         const InstDev I = TL ? IL : P.inst[b];
         const int nw = I.n * I.W;
-        if (held >= 0 && held != b) flush<WM>(P.ctl + held, C, lane);
+        if (held >= 0 && held != b) flush(P.ctl + held, held == sum_inst ? &wg_sum : nullptr, C, lane);
         held = b;
         if (kind == K_ROOT) {
             for (int t = lane; t < nw; t += 64) L.dom[t] = I.dom0[t];
@@ -2959,14 +3043,16 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
             for (int t = lane; t <= I.n; t += 64) L.trig[t] = I.trig_off[t];
         wsync();
         // the slot's words are in LDS now: hand the cell back to producers
-        if (s && lane == 0) st_rlx(&P.qseq[cell], pos + P.qmask + 1u);
+        if (s && lane == 0) st_rlx(s + SLOT_SEQ, pos + P.qmask + 1u);
         InstCtl *ctl = P.ctl + b;
-        int skip = 0;
-        if (lane == 0) {
-            const uint32_t sig = ld_rlx(&P.q->signal);
-            skip = (sig & SIG_STOP) ? 1 : ((sig & SIG_DONE) ? ld_rlx_i(&ctl->done) : 0);
+        uint32_t odds = 0u;
+        const uint32_t sig = wg_poll(P, &wgp, clk(), t_start, lane, &odds);
+        int skip = (sig & SIG_STOP) ? 1 : 0;
+        if (!skip && (sig & SIG_DONE)) {
+            if (lane == 0) skip = ld_rlx_i(&ctl->done);
+            skip = uni(skip);
         }
-        if (!uni(skip)) {
+        if (!skip) {
             if (VAR)
                 run_task_var<WM>(P, I, ctl, b, kind, F0, T, L, trail, C, lane, t_start, &wgp);
             else
@@ -2975,7 +3061,7 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
         C.tasks += 1;
         fold_var(C);
         if (I.max_nodes) {  // the budget counts every node at the task's end
-            flush<WM>(ctl, C, lane);
+            flush(ctl, nullptr, C, lane);
             held = -1;
         }
         T.rank = 0;
@@ -3006,10 +3092,31 @@ __global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_
             }
             direct = uni(nb);
         }
-        if (lane == 0) add_i(&P.g->pending, -1);
+        int last = 0;
+        // the task's stores (its queue cell's among them) come before its end
+        slot_stores_done();
+        if (lane == 0) last = add_i(&P.g->pending, -1);
+        if (uni(last) == 1) close_rings(P, lane);
     }
-    if (held >= 0) flush<WM>(P.ctl + held, C, lane);
-    if (lane == 0 && idle) add_u(&P.q->signal, 0xFFFFFFFFu);
+    if (held >= 0) flush(P.ctl + held, held == sum_inst ? &wg_sum : nullptr, C, lane);
+    if (sum_inst >= 0) {
+        // the last wave of the workgroup to leave adds its sums
+        uint32_t left = 0u;
+        if (lane == 0) left = __hip_atomic_fetch_sub(&waves_left, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (uniu(left) == 1u && lane == 0) {
+            InstCtl *ctl = P.ctl + sum_inst;
+            const auto add = [](auto *p, u64 v) {
+                if (v) add_u64(p, v);
+            };
+            add(&ctl->nodes, wg_sum.nodes);
+            add(&ctl->fails, wg_sum.fails);
+            add(&ctl->count, wg_sum.count);
+            add(&ctl->steals, wg_sum.steals);
+            add(&ctl->tasks, wg_sum.tasks);
+            add(&ctl->revisions, wg_sum.revisions);
+            add(&ctl->alg_bytes, wg_sum.alg_bytes);
+        }
+    }
 }
 
 #if CUBICS_ONLY_WM == 1
@@ -3053,16 +3160,16 @@ __global__ void init_kernel(SearchParams P) {
         const uint32_t r = c / cells, local = c % cells;
         const uint32_t on_ring = seeded > r ? (seeded - r + R - 1u) / R : 0u;
         if (local < on_ring) {
-            uint32_t *s = P.qdata + (size_t)c * P.slot_words;
+            uint32_t *s = P.qdata0 + (size_t)c * P.slot_words;
             s[0] = local * R + r;
             s[1] = (uint32_t)K_ROOT;
             s[2] = 0;
             s[3] = 0;
             for (int k = 0; k < 8 && 4 + k < SLOT_HDR; ++k) s[4 + k] = 0;
             s[12] = 0;
-            P.qseq[c] = local + 1u;
+            s[SLOT_SEQ] = local + 1u;
         } else {
-            P.qseq[c] = local;
+            P.qdata0[(size_t)c * P.slot_words + SLOT_SEQ] = local;
         }
     }
     for (uint32_t b = tid; b < (uint32_t)P.B; b += stride) {
@@ -3085,6 +3192,7 @@ __global__ void init_kernel(SearchParams P) {
         P.qb->ring[tid].signal = 0u;
         P.qb->ring[tid].groups = 0u;
     }
+    if (tid < QVIEWS) P.qb->view[tid].word = 0ull;
     if (tid == 0) {
         P.g->pending = P.team ? P.nblocks : (int32_t)seeded;
         P.g->produced = 0;
