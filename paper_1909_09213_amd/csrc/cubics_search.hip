@@ -56,29 +56,58 @@ DEV u64 uni64(u64 x) {
 }
 DEV long long unill(long long x) { return (long long)uni64((u64)x); }
 
+// Reductions over the wave by DPP: four shifts within rows of 16 lanes, then
+// two row broadcasts, six vector instructions whose result is read from lane
+// 63 into a scalar register.  (Through __shfl_xor each step is a trip to the
+// LDS, some hundred clocks, and the result stays in a vector register.)
+// Called with every lane active.  `none` is the operation's identity: what
+// lanes without a source see.
+template <int CTRL, int ROWS>
+DEV uint32_t dpp(uint32_t none, uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+DEV u64 dpp64(u64 none, u64 v) {
+    return ((u64)dpp<CTRL, ROWS>((uint32_t)(none >> 32), (uint32_t)(v >> 32)) << 32) |
+           dpp<CTRL, ROWS>((uint32_t)none, (uint32_t)v);
+}
+template <class OP>
+DEV uint32_t wave_reduce(uint32_t v, uint32_t none, OP op) {
+    v = op(v, dpp<0x111, 0xf>(none, v));  // row_shr:1
+    v = op(v, dpp<0x112, 0xf>(none, v));  // row_shr:2
+    v = op(v, dpp<0x114, 0xf>(none, v));  // row_shr:4
+    v = op(v, dpp<0x118, 0xf>(none, v));  // row_shr:8: lane 15 of a row holds the row's result
+    v = op(v, dpp<0x142, 0xa>(none, v));  // row_bcast:15 into rows 1 and 3
+    v = op(v, dpp<0x143, 0xc>(none, v));  // row_bcast:31 into rows 2 and 3
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+template <class OP>
+DEV u64 wave_reduce64(u64 v, u64 none, OP op) {
+    v = op(v, dpp64<0x111, 0xf>(none, v));
+    v = op(v, dpp64<0x112, 0xf>(none, v));
+    v = op(v, dpp64<0x114, 0xf>(none, v));
+    v = op(v, dpp64<0x118, 0xf>(none, v));
+    v = op(v, dpp64<0x142, 0xa>(none, v));
+    v = op(v, dpp64<0x143, 0xc>(none, v));
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63);
+    return ((u64)hi << 32) | lo;
+}
 DEV uint32_t wave_or(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v |= __shfl_xor(v, o, 64);
-    return v;
+    return wave_reduce(v, 0u, [](uint32_t a, uint32_t b) { return a | b; });
 }
 DEV int wave_sum(int v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return (int)wave_reduce((uint32_t)v, 0u, [](uint32_t a, uint32_t b) { return a + b; });
 }
-DEV long long wave_sum64(long long v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+DEV u64 wave_sumu64(u64 v) {
+    return wave_reduce64(v, 0ull, [](u64 a, u64 b) { return a + b; });
 }
-DEV u64 wave_sumu64(u64 v) { return (u64)wave_sum64((long long)v); }
+DEV long long wave_sum64(long long v) { return (long long)wave_sumu64((u64)v); }
 DEV uint32_t wave_min(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        uint32_t w = __shfl_xor(v, o, 64);
-        v = w < v ? w : v;
-    }
-    return v;
+    return wave_reduce(v, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+}
+DEV u64 wave_min64(u64 v) {
+    return wave_reduce64(v, ~0ull, [](u64 a, u64 b) { return a < b ? a : b; });
 }
 
 // -------------------------------------------------------------- atomics
@@ -1631,15 +1660,6 @@ DEV int var_pop(const InstDev &I, const Lds &L, int i) {
     for (int k = 0; k < WM; ++k)
         if (k < I.W) p += __popc(L.dom[i * I.W + k]);
     return p;
-}
-
-DEV u64 wave_min64(u64 v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const u64 w = __shfl_xor(v, o, 64);
-        v = w < v ? w : v;
-    }
-    return v;
 }
 
 DEV u64 mix64(u64 z) {  // SplitMix64 finalizer (Steele, Lea and Flood 2014)
