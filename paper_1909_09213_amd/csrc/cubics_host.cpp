@@ -252,6 +252,7 @@ extern "C" int cubics_load(cubics_ctx *ctx, int32_t n, const int32_t *lo, const 
 
     // ---- constraints
     std::vector<Unit> units;
+    const auto with_limit = [](int src, int limit) { return src | limit << 16; };
     // rows start with an all-ones block of 32 words: in the register layout
     // a lane with no constraint to the revised source (pair entry 0, row
     // offset 0) takes the support union of this block and keeps its domain.
@@ -325,8 +326,18 @@ extern "C" int cubics_load(cubics_ctx *ctx, int32_t n, const int32_t *lo, const 
                         }
                 const double t = 1.0 - (double)allowed / ((double)di * dj);
                 tight_sum[i] += t; tight_sum[j] += t;
-                units.push_back({i | (U_TABLE << 24), j, off_ij, off_ji});
-                units.push_back({j | (U_TABLE << 24), i, off_ji, off_ij});
+                // the most values of the source that one target value conflicts with
+                const auto limit = [&](int32_t off, int dt, int dsrc) {
+                    int lim = 0;
+                    for (int a = 0; a < dt; ++a) {
+                        int sup = 0;
+                        for (int w = 0; w < W; ++w) sup += __builtin_popcount(rows[off + (size_t)a * W + w]);
+                        lim = std::max(lim, dsrc - sup);
+                    }
+                    return lim;
+                };
+                units.push_back({i | (U_TABLE << 24), with_limit(j, limit(off_ij, di, dj)), off_ij, off_ji});
+                units.push_back({j | (U_TABLE << 24), with_limit(i, limit(off_ji, dj, di)), off_ji, off_ij});
             } else {
                 if (npar != 1 || !par) return fail(CUBICS_EINVAL, "constraint %d: needs 1 parameter", c);
                 const int64_t p = par[0];
@@ -334,17 +345,17 @@ extern "C" int cubics_load(cubics_ctx *ctx, int32_t n, const int32_t *lo, const 
                 const int32_t dl = (int32_t)((int64_t)lo[j] - lo[i] + (ty == CUBICS_QUEENS ? 0 : p));
                 if (ty == CUBICS_NEQ) {
                     // x_i != x_j + p: a = b + dl is removed from i; b = a - dl from j
-                    units.push_back({i | (U_NEQ << 24), j, dl, 0});
-                    units.push_back({j | (U_NEQ << 24), i, -dl, 0});
+                    units.push_back({i | (U_NEQ << 24), with_limit(j, 1), dl, 0});
+                    units.push_back({j | (U_NEQ << 24), with_limit(i, 1), -dl, 0});
                     tight_sum[i] += 1.0 / dj; tight_sum[j] += 1.0 / di;
                 } else if (ty == CUBICS_LT) {
-                    units.push_back({i | (U_LT_UB << 24), j, dl, 0});
-                    units.push_back({j | (U_LT_LB << 24), i, dl, 0});
+                    units.push_back({i | (U_LT_UB << 24), with_limit(j, CUBICS_MAX_DOMAIN), dl, 0});
+                    units.push_back({j | (U_LT_LB << 24), with_limit(i, CUBICS_MAX_DOMAIN), dl, 0});
                     tight_sum[i] += 0.5; tight_sum[j] += 0.5;
                 } else {
                     const int32_t kq = (int32_t)p;
-                    units.push_back({i | (U_QUEENS << 24), j, kq, (int32_t)(lo[j] - lo[i])});
-                    units.push_back({j | (U_QUEENS << 24), i, kq, (int32_t)(lo[i] - lo[j])});
+                    units.push_back({i | (U_QUEENS << 24), with_limit(j, 3), kq, (int32_t)(lo[j] - lo[i])});
+                    units.push_back({j | (U_QUEENS << 24), with_limit(i, 3), kq, (int32_t)(lo[i] - lo[j])});
                     tight_sum[i] += 3.0 / dj; tight_sum[j] += 3.0 / di;
                 }
             }
@@ -455,12 +466,12 @@ extern "C" int cubics_load(cubics_ctx *ctx, int32_t n, const int32_t *lo, const 
 
     // ---- units sorted by source variable (stable), trigger ranges
     std::vector<int32_t> trig_off(n + 1, 0);
-    for (const Unit &u : units) trig_off[u.src + 1]++;
+    for (const Unit &u : units) trig_off[(u.src & 0xFFFF) + 1]++;
     for (int i = 0; i < n; ++i) trig_off[i + 1] += trig_off[i];
     std::vector<Unit> sorted(units.size());
     {
         std::vector<int32_t> fill(trig_off.begin(), trig_off.end() - 1);
-        for (const Unit &u : units) sorted[fill[u.src]++] = u;
+        for (const Unit &u : units) sorted[fill[u.src & 0xFFFF]++] = u;
     }
     // ---- global trigger lists
     std::vector<int32_t> gtrig_off(n + 1, 0), gtrig;
@@ -493,7 +504,7 @@ extern "C" int cubics_load(cubics_ctx *ctx, int32_t n, const int32_t *lo, const 
         pairs.assign((size_t)n * 64, 0u);
         const int32_t P28 = 1 << 27;  // parameters are 28-bit signed
         for (const Unit &u : sorted) {
-            const int t = u.tt & 0xFFFFFF, ty = u.tt >> 24, j = u.src;
+            const int t = u.tt & 0xFFFFFF, ty = u.tt >> 24, j = u.src & 0xFFFF;
             uint32_t &e = pairs[(size_t)j * 64 + t];
             if (e != 0u) { var_ok = false; break; }  // two constraints on one pair
             uint32_t prm = 0;
@@ -680,7 +691,7 @@ Geometry geometry(cubics_prob *const *probs, int B) {
     int words = ((g.nmax * g.wmax) + 1) & ~1;
     words += 2 * ndw + 2 * ndw + 2 * ngw + ((g.nmax + 1) & ~1) + ((g.nmax + 2) & ~1) +
              (g.gac ? SCRATCH_GAC_WORDS : SCRATCH_WORDS);
-    g.lds_words = (words + 1) & ~1;
+    g.lds_words = (words + 3) & ~3;
     return g;
 }
 
@@ -784,7 +795,7 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
     const size_t per_wave = (size_t)lds_words * 4;
     const size_t pol_bytes = feat == 1 ? 2 * (size_t)POLICY_LDS_WORDS * 4 : 0;  // network copies
     const size_t tab_bytes = (B == 1) ? (size_t)probs[0]->dev.blob_words * 4 : 0;
-    bool tl = B == 1 && L0.tables_in_lds != 2 && tab_bytes + pol_bytes + per_wave <= LDS_WG_MAX;
+    const bool tl = B == 1 && L0.tables_in_lds != 2 && tab_bytes + pol_bytes + per_wave <= LDS_WG_MAX;
     size_t lds = (tl ? tab_bytes : 0) + pol_bytes + per_wave * wpb;
     while (wpb > 1 && lds > LDS_WG_MAX) {
         wpb /= 2;
@@ -1231,7 +1242,9 @@ extern "C" int cubics_root(cubics_prob *p, int32_t layout, uint32_t *out_bits, i
     SearchParams P;
     memset(&P, 0, sizeof P);
     P.inst = (const InstDev *)ctx->inst.p;
-    P.layout = choose_layout(arr, 1, layout);
+    // (one lane per unit unless the caller asks otherwise: every variable is
+    // dirty at a root, and most units are looked at without reading a row)
+    P.layout = layout == CUBICS_LAYOUT_AUTO ? CUBICS_LAYOUT_LANE : choose_layout(arr, 1, layout);
     P.lds_words = G.lds_words;
     P.nmax = G.nmax;
     P.wmax = G.wmax;
@@ -1239,7 +1252,7 @@ extern "C" int cubics_root(cubics_prob *p, int32_t layout, uint32_t *out_bits, i
     uint32_t *dout = (uint32_t *)ctx->rootout.p;
     int32_t *dfail = (int32_t *)((char *)ctx->rootout.p + nw * 4);
     unsigned long long *drev = (unsigned long long *)((char *)ctx->rootout.p + nw * 4 + 8);
-    HIPCHK(launch_root(G.wmax, P, dout, dfail, drev, (size_t)G.lds_words * 4, ctx->stream));
+    HIPCHK(launch_root(G.wmax, P, dout, dfail, drev, (size_t)P.lds_words * 4, ctx->stream));
     HIPCHK(hipMemcpyAsync(out_bits, dout, (size_t)p->n * p->W * 4, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipMemcpyAsync(failed, dfail, 4, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));

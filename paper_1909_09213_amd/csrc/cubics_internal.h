@@ -26,7 +26,9 @@ constexpr int SCRATCH_GAC_WORDS = 96;  // ... when a GAC all-different is presen
 // (28-bit signed); QUEENS param = k << 15 | (delta & 0x7FFF).
 enum TaskKind : int32_t { K_ROOT = 0, K_NODE = 1, K_FRAME = 2 };
 
-// Binary unit (16 B).  tt = target var | type << 24.
+// Binary unit (16 B).  tt = target var | type << 24.  src = source var |
+// limit << 16: while the source holds more values than the limit, every target
+// value keeps a support and a revision removes nothing.
 // TABLE: p0 = word offset of rows indexed by target value (bits over source),
 //        p1 = word offset of rows indexed by source value (bits over target).
 struct Unit {

@@ -179,12 +179,30 @@ DEV bool cas_i(int32_t *p, int expected, int desired) {
 }
 
 // ---------------------------------------------------------- bit helpers
+// Is word k of a domain inside its W words (W <= WM)?  Known for the first
+// word, and so for every word of the one-word kernels.
+template <int WM>
+DEV bool in_w(int k, int W) { return k == 0 || k < W; }
+
+// The words of variable v's domain in LDS, zero past W.  Up to two words are
+// read together and masked (the word behind a one-word domain lies in LDS
+// too): a branch for the second word cost more than the read.
+template <int WM>
+DEV void ld_dom(const uint32_t *dom, int v, int W, uint32_t (&d)[WM]) {
+    if constexpr (WM <= 2) {
+        const uint32_t *p = dom + v * W;
+#pragma unroll
+        for (int k = 0; k < WM; ++k) d[k] = k == 0 ? p[k] : p[k] & (W > k ? ~0u : 0u);
+    } else {
+#pragma unroll
+        for (int k = 0; k < WM; ++k) d[k] = in_w<WM>(k, W) ? dom[v * W + k] : 0u;
+    }
+}
 template <int WM>
 DEV int pop_w(const uint32_t (&d)[WM], int W) {
     int s = 0;
 #pragma unroll
-    for (int k = 0; k < WM; ++k)
-        if (k < W) s += __popc(d[k]);
+    for (int k = 0; k < WM; ++k) s += __popc(d[k]);  // words past W are zero
     return s;
 }
 template <int WM>
@@ -192,7 +210,7 @@ DEV int low_w(const uint32_t (&d)[WM], int W) {  // lowest set index, -1 if empt
     int r = -1;
 #pragma unroll
     for (int k = WM - 1; k >= 0; --k)
-        if (k < W && d[k]) r = 32 * k + __ffs(d[k]) - 1;
+        if (d[k]) r = 32 * k + __ffs(d[k]) - 1;
     return r;
 }
 template <int WM>
@@ -200,7 +218,7 @@ DEV int high_w(const uint32_t (&d)[WM], int W) {  // highest set index, -1 if em
     int r = -1;
 #pragma unroll
     for (int k = 0; k < WM; ++k)
-        if (k < W && d[k]) r = 32 * k + 31 - __clz(d[k]);
+        if (d[k]) r = 32 * k + 31 - __clz(d[k]);
     return r;
 }
 // mask of indices <= ub (ub may be negative or >= 32W)
@@ -272,15 +290,38 @@ DEV Unit ld_unit(const Unit *p, uint32_t i) {
 template <int WM>
 constexpr int row_batch() { return WM <= 2 ? CUBICS_RB_NARROW : (WM == 4 ? 4 : 2); }
 
-// Word k of row j - 1 of a row block, j >= 0: rm points at the block's row
-// -1 (the zero words before it), stride is the row length in bytes.  One
-// unsigned 32 x 32 + 64-bit multiply-add gives a row's address; the words of
-// a row then differ only by an immediate offset.
-template <bool GM>
-DEV uint32_t ld_row(const uint32_t *rm, uint32_t j, uint32_t stride, int k) {
+// Row j - 1 of a row block, j >= 0: rm points at the block's row -1 (the zero
+// words before it), stride is the row length in bytes.  One unsigned 32 x 32 +
+// 64-bit multiply-add gives a row's address.  Two-word rows are read at once
+// (4-byte aligned; the second word is masked where rows have one: the word
+// behind a row lies inside the packed problem).
+template <bool GM, int WM>
+DEV void ld_row(const uint32_t *rm, uint32_t j, uint32_t stride, int W, uint32_t (&r)[WM]) {
     const char *a = (const char *)rm + (unsigned long long)j * stride;
-    if constexpr (GM) return ((const __attribute__((address_space(1))) uint32_t *)a)[k];
-    else return ((const uint32_t *)a)[k];
+    if constexpr (WM == 2) {
+        struct __attribute__((packed, aligned(4))) two {
+            uint32_t x, y;
+        };
+        two t;
+        if constexpr (GM) {
+            t.x = ((const __attribute__((address_space(1))) uint32_t *)a)[0];
+            t.y = ((const __attribute__((address_space(1))) uint32_t *)a)[1];
+        } else {
+            t.x = ((const uint32_t *)a)[0];
+            t.y = ((const uint32_t *)a)[1];
+        }
+        r[0] = t.x;
+        r[1] = t.y & (W > 1 ? ~0u : 0u);
+    } else {
+#pragma unroll
+        for (int k = 0; k < WM; ++k) {
+            r[k] = 0u;
+            if (in_w<WM>(k, W)) {
+                if constexpr (GM) r[k] = ((const __attribute__((address_space(1))) uint32_t *)a)[k];
+                else r[k] = ((const uint32_t *)a)[k];
+            }
+        }
+    }
 }
 
 // The next R live values of word w of a domain, as value index + 1 (0 once
@@ -303,9 +344,7 @@ DEV void union_batch(const uint32_t *rm, uint32_t stride, uint32_t &bits, int w,
     next_values<R>(bits, w, ix);
     uint32_t r[R][WM];
 #pragma unroll
-    for (int q = 0; q < R; ++q)
-#pragma unroll
-        for (int k = 0; k < WM; ++k) r[q][k] = k < W ? ld_row<GM>(rm, ix[q], stride, k) : 0u;
+    for (int q = 0; q < R; ++q) ld_row<GM, WM>(rm, ix[q], stride, W, r[q]);
 #pragma unroll
     for (int q = 0; q < R; ++q)
 #pragma unroll
@@ -321,9 +360,7 @@ DEV void test_batch(const uint32_t *rm, uint32_t stride, uint32_t &bits, int w, 
     next_values<R>(bits, w, ix);
     uint32_t r[R][WM];
 #pragma unroll
-    for (int q = 0; q < R; ++q)
-#pragma unroll
-        for (int k = 0; k < WM; ++k) r[q][k] = k < W ? ld_row<GM>(rm, ix[q], stride, k) : 0u;
+    for (int q = 0; q < R; ++q) ld_row<GM, WM>(rm, ix[q], stride, W, r[q]);
 #pragma unroll
     for (int q = 0; q < R; ++q) {
         uint32_t hit = 0u;
@@ -347,14 +384,15 @@ DEV void test_batch(const uint32_t *rm, uint32_t stride, uint32_t &bits, int w, 
 // row traffic).
 template <int WM, bool GM>
 DEV void revise_lane(const InstDev &I, const Unit &u, const uint32_t (&ds)[WM],
-                     const uint32_t (&dt)[WM], uint32_t (&nw)[WM], int W, int *rows_read) {
+                     const uint32_t (&dt)[WM], uint32_t (&nw)[WM], int W, int ps, int pt, int *rows_read) {
     const int ty = u.tt >> 24;
     constexpr int RB = row_batch<WM>();
 #pragma unroll
     for (int k = 0; k < WM; ++k) nw[k] = dt[k];
     *rows_read = 0;
-    if (ty == U_TABLE) {
-        const int ps = pop_w(ds, W), pt = pop_w(dt, W);
+    // (the types that occur are known per instance: the branches on them are
+    // the wave's, not the lanes')
+    if ((I.unit_types & (1 << U_TABLE)) && ty == U_TABLE) {
         const uint32_t stride = 4u * (uint32_t)W;
         const uint32_t *rs = I.rows + (uint32_t)u.p1 - W;  // row -1, rows by source value
         const uint32_t *rt = I.rows + (uint32_t)u.p0 - W;  // row -1, rows by target value
@@ -366,7 +404,7 @@ DEV void revise_lane(const InstDev &I, const Unit &u, const uint32_t (&ds)[WM],
         uint32_t b0 = 0u;
 #pragma unroll
         for (int k = WM - 1; k >= 0; --k)
-            if (k < W && ds[k]) w0 = k;
+            if (ds[k]) w0 = k;
 #pragma unroll
         for (int k = 0; k < WM; ++k) b0 = (k == w0) ? ds[k] : b0;
         const int n0 = __popc(b0);
@@ -379,14 +417,15 @@ DEV void revise_lane(const InstDev &I, const Unit &u, const uint32_t (&ds)[WM],
         *rows_read = (direct ? 0 : min(n0, RB)) + pop_w(open, W);
 #pragma unroll
         for (int w = 0; w < WM; ++w) {
-            if (w >= W) break;
             uint32_t bits = open[w];
             while (bits) test_batch<RB, WM, GM>(rt, stride, bits, w, W, ds, keep[w]);
         }
 #pragma unroll
         for (int k = 0; k < WM; ++k) nw[k] = (dt[k] & acc[k]) | keep[k];
-    } else if (ty == U_NEQ) {
-        if (pop_w(ds, W) == 1) {
+    }
+    if (!(I.unit_types & ~(1 << U_TABLE))) return;
+    if (ty == U_NEQ) {
+        if (ps == 1) {
             int a = low_w(ds, W) + u.p0;
 #pragma unroll
             for (int k = 0; k < WM; ++k) nw[k] = dt[k] & ~bit_in_word(a, k);
@@ -400,7 +439,7 @@ DEV void revise_lane(const InstDev &I, const Unit &u, const uint32_t (&ds)[WM],
 #pragma unroll
         for (int k = 0; k < WM; ++k) nw[k] = dt[k] & mask_ge(lb, k);
     } else if (ty == U_QUEENS) {
-        if (pop_w(ds, W) <= 3) {
+        if (ps <= 3) {
             // unsupported = intersection over b in D_src of {b+d, b+d+k, b+d-k}
             uint32_t uns[WM];
 #pragma unroll
@@ -408,7 +447,6 @@ DEV void revise_lane(const InstDev &I, const Unit &u, const uint32_t (&ds)[WM],
             const int kk = u.p0, dl = u.p1;
 #pragma unroll
             for (int w = 0; w < WM; ++w) {
-                if (w >= W) break;
                 uint32_t bits = ds[w];
                 while (bits) {
                     int b = 32 * w + __ffs(bits) - 1 + dl;
@@ -473,41 +511,61 @@ struct Lds {
     float *vscr;     // [VALUE_LDS_WORDS] learned value order: value features, then scores
 };
 
+DEV int unit_src(const Unit &u) { return u.src & 0xFFFF; }
+DEV int unit_limit(const Unit &u) { return (int)((uint32_t)u.src >> 16); }
+
+// Can a revision of the unit remove something, its source holding ps values and
+// its target pt?
+//  - Only while ps is within the unit's limit: the most values of the source
+//    that any one target value conflicts with (tables; 3 for a queens pair, 1
+//    for !=).  With more, every target value keeps a support.
+//  - Only if the target has two values or more, or both have one.  A target
+//    with one value v needs no revision against a source y with more: when it
+//    got v it became dirty, so y is revised against v before the fixpoint, and
+//    D_y then lies inside v's supports; had v no support left in D_y, that
+//    revision empties D_y, the same failure.
+// The lanes left out load no rows: scattered row loads, one cache access a
+// lane and row, bound the search of instances whose tables lie in memory.
+// 1,024 sweep instances 320 -> 290 ms, a root of 120 variables with 64 values
+// 6.6 -> 0.22 ms.  (Rows in LDS are cheaper than the test: not used there.)
+DEV bool may_remove(const Unit &u, int ps, int pt) { return ps <= unit_limit(u) && (pt >= 2 || ps == 1); }
+
 // Process one chunk of binary units in LANE layout.  Returns wave-uniform fail.
 template <int WM, bool GM>
-DEV bool chunk_lane(const InstDev &I, const Lds &L, u64 *nxt, int my_u, Counters &C, int lane) {
+DEV bool chunk_lane(const InstDev &I, const Lds &L, u64 *nxt, int my_u, Counters &C) {
     const int W = I.W;
     bool changed = false;
     int tgt = 0;
     if (my_u >= 0) {
         const Unit u = ld_unit<GM>(I.units, (uint32_t)my_u);
         tgt = u.tt & 0xFFFFFF;
+        const int src = unit_src(u);
         uint32_t ds[WM], dt[WM], nw[WM];
+        ld_dom<WM>(L.dom, src, W, ds);
+        ld_dom<WM>(L.dom, tgt, W, dt);
+        const int ps = pop_w(ds, W), pt = pop_w(dt, W);
+        if (!GM || may_remove(u, ps, pt)) {
+            int rows_read = 0;
+            revise_lane<WM, GM>(I, u, ds, dt, nw, W, ps, pt, &rows_read);
 #pragma unroll
-        for (int k = 0; k < WM; ++k) {
-            ds[k] = k < W ? L.dom[u.src * W + k] : 0u;
-            dt[k] = k < W ? L.dom[tgt * W + k] : 0u;
+            for (int k = 0; k < WM; ++k) changed |= nw[k] != dt[k];
+            C.rev += 1;
+            C.bytes += rev_bytes(W, rows_read, changed);
         }
-        int rows_read = 0;
-        revise_lane<WM, GM>(I, u, ds, dt, nw, W, &rows_read);
-#pragma unroll
-        for (int k = 0; k < WM; ++k) changed |= (k < W) && nw[k] != dt[k];
-        C.rev += 1;
-        C.bytes += rev_bytes(W, rows_read, changed);
         if (changed) {
 #pragma unroll
             for (int k = 0; k < WM; ++k)
-                if (k < W && nw[k] != dt[k]) atomicAnd(&L.dom[tgt * W + k], nw[k]);
+                if (nw[k] != dt[k]) atomicAnd(&L.dom[tgt * W + k], nw[k]);
             atomicOr(&nxt[tgt >> 6], 1ull << (tgt & 63));
         }
     }
     wsync();
     bool empty = false;
     if (changed) {
-        uint32_t acc = 0;
+        uint32_t d[WM], acc = 0;
+        ld_dom<WM>(L.dom, tgt, W, d);
 #pragma unroll
-        for (int k = 0; k < WM; ++k)
-            if (k < W) acc |= L.dom[tgt * W + k];
+        for (int k = 0; k < WM; ++k) acc |= d[k];
         empty = acc == 0;
     }
     return __ballot(empty) != 0;
@@ -519,27 +577,29 @@ DEV bool chunk_seg(const InstDev &I, const Lds &L, u64 *nxt, int my_u, int sh, C
     const int W = I.W;
     const int S = 1 << sh;
     const int slot = lane >> sh, a = lane & (S - 1);
-    bool sup = false;
+    bool sup = false, need = false;
     Unit u = {0, 0, 0, 0};
     uint32_t dt[WM];
 #pragma unroll
     for (int k = 0; k < WM; ++k) dt[k] = 0u;
     if (my_u >= 0) {
         u = ld_unit<GM>(I.units, (uint32_t)my_u);
-        const int tgt = u.tt & 0xFFFFFF;
+        const int tgt = u.tt & 0xFFFFFF, src = unit_src(u);
         uint32_t ds[WM];
 #pragma unroll
         for (int k = 0; k < WM; ++k) {
-            ds[k] = k < W ? L.dom[u.src * W + k] : 0u;
+            ds[k] = k < W ? L.dom[src * W + k] : 0u;
             dt[k] = k < W ? L.dom[tgt * W + k] : 0u;
         }
         const bool live = (a < 32 * W) && ((dt[a >> 5] >> (a & 31)) & 1u);
-        if (live) sup = supported_seg<WM, GM>(I, u, ds, a, W);
+        need = !GM || may_remove(u, pop_w(ds, W), pop_w(dt, W));
+        sup = live;
+        if (live && need) sup = supported_seg<WM, GM>(I, u, ds, a, W);
     }
     const u64 m = __ballot(sup);
     bool changed = false;
     int tgt = u.tt & 0xFFFFFF;
-    if (my_u >= 0 && a == 0) {
+    if (need && a == 0) {
         const u64 seg = sh == 6 ? m : ((m >> (slot << sh)) & ((1ull << S) - 1ull));
         uint32_t nw[WM];
 #pragma unroll
@@ -617,7 +677,7 @@ DEV bool revise_alldiff(const InstDev &I, const GDesc &g, const Lds &L, u64 *nxt
         const int v = sc[t];
         uint32_t d[WM];
 #pragma unroll
-        for (int w = 0; w < WM; ++w) d[w] = w < W ? L.dom[v * W + w] : 0u;
+        for (int w = 0; w < WM; ++w) d[w] = in_w<WM>(w, W) ? L.dom[v * W + w] : 0u;
         if (pop_w(d, W) == 1) {
             ++nsing;
             const int sft = I.lo[v] - base;
@@ -653,7 +713,7 @@ DEV bool revise_alldiff(const InstDev &I, const GDesc &g, const Lds &L, u64 *nxt
         const int sft = I.lo[v] - base;
         uint32_t d[WM];
 #pragma unroll
-        for (int w = 0; w < WM; ++w) d[w] = w < W ? L.dom[v * W + w] : 0u;
+        for (int w = 0; w < WM; ++w) d[w] = in_w<WM>(w, W) ? L.dom[v * W + w] : 0u;
         if (pop_w(d, W) >= 2) {
             uint32_t Uv[WM];
             if (sft) {
@@ -739,7 +799,7 @@ DEV bool revise_alldiff_gac(const InstDev &I, const GDesc &g, const Lds &L, u64 
     const int sft = act ? I.lo[v] - base : 0;
     uint32_t d[WM], Dv[WM];
 #pragma unroll
-    for (int w = 0; w < WM; ++w) d[w] = (act && w < W) ? L.dom[v * W + w] : 0u;
+    for (int w = 0; w < WM; ++w) d[w] = (act && in_w<WM>(w, W)) ? L.dom[v * W + w] : 0u;
     if (sft) {
         shl_w(d, sft, Dv);
     } else {
@@ -898,7 +958,7 @@ DEV bool revise_linear(const InstDev &I, const GDesc &g, const Lds &L, u64 *nxt,
         const int v = sc[t];
         uint32_t d[WM];
 #pragma unroll
-        for (int w = 0; w < WM; ++w) d[w] = w < W ? L.dom[v * W + w] : 0u;
+        for (int w = 0; w < WM; ++w) d[w] = in_w<WM>(w, W) ? L.dom[v * W + w] : 0u;
         part += (long long)co[1 + t] * (long long)(I.lo[v] + low_w(d, W));
     }
     const long long S = wave_sum64(part);
@@ -909,7 +969,7 @@ DEV bool revise_linear(const InstDev &I, const GDesc &g, const Lds &L, u64 *nxt,
         const int v = sc[t];
         uint32_t d[WM];
 #pragma unroll
-        for (int w = 0; w < WM; ++w) d[w] = w < W ? L.dom[v * W + w] : 0u;
+        for (int w = 0; w < WM; ++w) d[w] = in_w<WM>(w, W) ? L.dom[v * W + w] : 0u;
         const long long at = co[1 + t];
         const long long mn = (long long)I.lo[v] + low_w(d, W);
         const long long slack = b - (S - at * mn);  // >= at * mn, since S <= b
@@ -1012,7 +1072,7 @@ DEV bool revise_linear_ad(const InstDev &I, const GDesc &g, const Lds &L, u64 *n
         const int v = sc[t];
         uint32_t d[WM];
 #pragma unroll
-        for (int w = 0; w < WM; ++w) d[w] = w < W ? L.dom[v * W + w] : 0u;
+        for (int w = 0; w < WM; ++w) d[w] = in_w<WM>(w, W) ? L.dom[v * W + w] : 0u;
         part += (long long)co[1 + t] * (long long)(I.lo[v] + low_w(d, W));
     }
     long long S = wave_sum64(part), excess = 0;
@@ -1031,7 +1091,7 @@ DEV bool revise_linear_ad(const InstDev &I, const GDesc &g, const Lds &L, u64 *n
             const int t = pos[lane], v = sc[t];
             uint32_t d[WM];
 #pragma unroll
-            for (int w = 0; w < WM; ++w) d[w] = w < W ? L.dom[v * W + w] : 0u;
+            for (int w = 0; w < WM; ++w) d[w] = in_w<WM>(w, W) ? L.dom[v * W + w] : 0u;
             pg = (long long)co[1 + t] * (long long)(I.lo[v] + low_w(d, W));
             const int sft = I.lo[v] - base;
             if (sft) {
@@ -1079,7 +1139,7 @@ DEV bool revise_linear_ad(const InstDev &I, const GDesc &g, const Lds &L, u64 *n
         const int v = sc[t];
         uint32_t d[WM];
 #pragma unroll
-        for (int w = 0; w < WM; ++w) d[w] = w < W ? L.dom[v * W + w] : 0u;
+        for (int w = 0; w < WM; ++w) d[w] = in_w<WM>(w, W) ? L.dom[v * W + w] : 0u;
         const long long at = co[1 + t];
         const long long mn = (long long)I.lo[v] + low_w(d, W);
         linear_cut<WM>(I, L, nxt, C, v, d, at, b - (S - at * mn));
@@ -1093,7 +1153,7 @@ DEV bool revise_linear_ad(const InstDev &I, const GDesc &g, const Lds &L, u64 *n
             const int t = pos[lane], v = sc[t];
             uint32_t d[WM];
 #pragma unroll
-            for (int w = 0; w < WM; ++w) d[w] = w < W ? L.dom[v * W + w] : 0u;
+            for (int w = 0; w < WM; ++w) d[w] = in_w<WM>(w, W) ? L.dom[v * W + w] : 0u;
             const long long at = co[1 + t];
             const long long mn = (long long)I.lo[v] + low_w(d, W);
             linear_cut<WM>(I, L, nxt, C, v, d, at, b - (S - ex - at * mn));
@@ -1116,7 +1176,7 @@ DEV bool propagate(const InstDev &I, const Lds &L, int layout, Counters &C, int 
     const int ndw = (n + 63) >> 6, ngw = (I.n_glob + 63) >> 6;
     const bool seg = SEGC && layout == 2 && I.seg_ok;
     const int sh = seg ? (31 - __clz(I.S)) : 0;
-    const int CH = seg ? (64 >> sh) : 64;
+    const int CH = seg ? (64 >> sh) : 64;  // units per chunk
     const int slot = seg ? (lane >> sh) : lane;
     u64 *cur = L.dA, *nxt = L.dB;
     for (;;) {
@@ -1139,7 +1199,7 @@ DEV bool propagate(const InstDev &I, const Lds &L, int layout, Counters &C, int 
                     beg += take;
                     if (cnt == CH) {
                         fail = (SEGC && seg) ? chunk_seg<WM, GM>(I, L, nxt, my_u, sh, C, lane)
-                                             : chunk_lane<WM, GM>(I, L, nxt, my_u, C, lane);
+                                             : chunk_lane<WM, GM>(I, L, nxt, my_u, C);
                         cnt = 0;
                         my_u = -1;
                         if (fail) break;
@@ -1156,7 +1216,7 @@ DEV bool propagate(const InstDev &I, const Lds &L, int layout, Counters &C, int 
         }
         if (!fail && cnt > 0)
             fail = (SEGC && seg) ? chunk_seg<WM, GM>(I, L, nxt, my_u, sh, C, lane)
-                                 : chunk_lane<WM, GM>(I, L, nxt, my_u, C, lane);
+                                 : chunk_lane<WM, GM>(I, L, nxt, my_u, C);
         if (fail) return true;
         if (GLOB && I.n_glob) {
             wsync();
@@ -1204,7 +1264,7 @@ DEV int var_pop(const InstDev &I, const Lds &L, int i) {
     int p = 0;
 #pragma unroll
     for (int k = 0; k < WM; ++k)
-        if (k < I.W) p += __popc(L.dom[i * I.W + k]);
+        if (in_w<WM>(k, I.W)) p += __popc(L.dom[i * I.W + k]);
     return p;
 }
 
@@ -1222,7 +1282,7 @@ DEV int node_test(const InstDev &I, const Lds &L, int lane, int *bx, bool *one) 
         if (i < n) {
 #pragma unroll
             for (int k = 0; k < WM; ++k)
-                if (k < W) p += __popc(L.dom[i * W + k]);
+                if (in_w<WM>(k, W)) p += __popc(L.dom[i * W + k]);
             empty |= p == 0;
         }
         if (p >= 2) {
@@ -1420,7 +1480,7 @@ DEV void record_solution(const SearchParams &P, const InstDev &I, InstCtl *ctl, 
                 for (int i = lane; i < n; i += 64) {
                     uint32_t d[WM];
 #pragma unroll
-                    for (int k = 0; k < WM; ++k) d[k] = k < W ? L.dom[i * W + k] : 0u;
+                    for (int k = 0; k < WM; ++k) d[k] = in_w<WM>(k, W) ? L.dom[i * W + k] : 0u;
                     I.sol_buf[i] = I.lo[i] + low_w(d, W);
                 }
             fence_rel();
@@ -1443,7 +1503,7 @@ DEV void record_solution(const SearchParams &P, const InstDev &I, InstCtl *ctl, 
             for (int i = lane; i < n; i += 64) {
                 uint32_t d[WM];
 #pragma unroll
-                for (int k = 0; k < WM; ++k) d[k] = k < W ? L.dom[i * W + k] : 0u;
+                for (int k = 0; k < WM; ++k) d[k] = in_w<WM>(k, W) ? L.dom[i * W + k] : 0u;
                 row[i] = I.lo[i] + low_w(d, W);
             }
         }
@@ -1966,7 +2026,7 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
             uint32_t dx[WM];
 #pragma unroll
             for (int k = 0; k < WM; ++k) {
-                dx[k] = k < W ? uniu(L.dom[x * W + k]) & own[k] : 0u;
+                dx[k] = in_w<WM>(k, W) ? uniu(L.dom[x * W + k]) & own[k] : 0u;
                 own[k] = 0xFFFFFFFFu;
             }
             deepest = depth > deepest ? depth : deepest;
@@ -2204,7 +2264,7 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
             int m = 0;
 #pragma unroll
             for (int k = 0; k < WM; ++k) {
-                dx[k] = k < W ? uniu(L.dom[x * W + k]) : 0u;
+                dx[k] = in_w<WM>(k, W) ? uniu(L.dom[x * W + k]) : 0u;
                 m += __popc(dx[k]);
             }
             if (!P.two_way && T.size <= m) {
@@ -2463,14 +2523,20 @@ DEV bool propagate_var(const InstDev &I, uint32_t &d, u64 cur, Counters &C, int 
 
 // First-fail over the register domains (none of them empty: propagation saw
 // to that): 0 open (*bx, and whether it is the only open variable in *one),
-// 1 solution.  The smallest key over the lanes by DPP: a ballot for each
-// domain size up to the smallest took 5 scalar instructions a size, on the
-// unit that bounds this layout.
+// 1 solution.  A domain of two values, the most frequent choice deep in a
+// tree, is found by a ballot; else the smallest key over the lanes by DPP (a
+// ballot for each size took 5 scalar instructions a size, on the unit that
+// bounds this layout).
 DEV int node_test_var(uint32_t d, int lane, int *bx, bool *one) {
     const uint32_t pop = (uint32_t)__popc(d);  // 0 on lanes >= n
     const u64 open = __ballot(pop >= 2u);
     if (!open) return 1;
     *one = (open & (open - 1ull)) == 0ull;
+    const u64 two = __ballot(pop == 2u);
+    if (two) {
+        *bx = __ffsll((long long)two) - 1;
+        return 0;
+    }
     *bx = (int)(wave_min(pop >= 2u ? (pop << 6) | (uint32_t)lane : 0xFFFFFFFFu) & 63u);
     return 0;
 }
@@ -2823,6 +2889,12 @@ DEV InstDev rebase(const InstDev &g, const uint32_t *tab) {
 #ifndef CUBICS_LB_WAVES
 #define CUBICS_LB_WAVES 4
 #endif
+// ... of its plain first-fail kernels without global constraints, which need
+// the fewest registers: the sweep's kernel at five waves runs 1,024 instances
+// in 245 ms, at four in 275.
+#ifndef CUBICS_LB_WAVES_PLAIN
+#define CUBICS_LB_WAVES_PLAIN 5
+#endif
 // ... and of the register layout, whose nodes wait on each other alone: six
 // waves per SIMD hide more of it.
 #ifndef CUBICS_LB_WAVES_VAR
@@ -2833,7 +2905,7 @@ DEV InstDev rebase(const InstDev &g, const uint32_t *tab) {
 // the global queue until no task is pending anywhere.  TL: a single-instance
 // solve whose packed tables are staged once per workgroup in LDS.
 template <int WM, bool TL, int FEAT, bool GLOB, bool SEGC, bool VAR = false>
-__global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM <= 2 ? CUBICS_LB_WAVES : 1)) void search_kernel(SearchParams P) {
+__global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM > 2 ? 1 : FEAT == 0 && !GLOB && !SEGC ? CUBICS_LB_WAVES_PLAIN : CUBICS_LB_WAVES)) void search_kernel(SearchParams P) {
     // 16-byte alignment: the words behind hold 64-bit sets that lanes update
     // with 64-bit atomics, and the tables are staged by 16-byte stores
     extern __shared__ __align__(16) uint32_t lds_raw[];
