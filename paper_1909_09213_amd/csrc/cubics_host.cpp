@@ -94,6 +94,7 @@ struct cubics_ctx {
     DevBuf lnsdom, lnssol;  // large-neighbourhood search: initial domains, solutions
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     int32_t *cancel_host = nullptr;  // pinned, polled by the kernel
+    mutable TrainStage stage;        // pinned words behind the flag's line
     struct Tuned {
         int layout;  // revision layout
         int div;     // workers = the occupancy-limited maximum / div
@@ -119,6 +120,7 @@ struct cubics_prob {
 
 hipStream_t cubics_ctx_stream(const cubics_ctx *c) { return c->stream; }
 int cubics_ctx_device(const cubics_ctx *c) { return c->device; }
+TrainStage *cubics_ctx_stage(const cubics_ctx *c) { return &c->stage; }
 
 // ----------------------------------------------------------------- context
 extern "C" int cubics_create(int32_t device, void *hip_stream, cubics_ctx **out) {
@@ -143,11 +145,12 @@ extern "C" int cubics_create(int32_t device, void *hip_stream, cubics_ctx **out)
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0)
         c->wall_khz = khz;
     if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess ||
-        hipHostMalloc((void **)&c->cancel_host, sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
+        hipHostMalloc((void **)&c->cancel_host, 64 + 4 * (POLICY_NP + 1), hipHostMallocDefault) != hipSuccess) {
         cubics_destroy(c);
         return fail(CUBICS_EDEVICE, "event / pinned flag allocation failed");
     }
     *c->cancel_host = 0;
+    c->stage.words = (float *)((char *)c->cancel_host + 64);
     *out = c;
     return CUBICS_OK;
 }

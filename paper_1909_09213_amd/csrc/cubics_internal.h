@@ -3,6 +3,8 @@
 #pragma once
 #include <stdint.h>
 
+#include <mutex>
+
 namespace cubics {
 
 // Propagator ("unit") types of binary constraints, one unit per direction.
@@ -207,5 +209,12 @@ constexpr int TRACE_WORDS = 8;
 constexpr int VALUE_MAX = 64;
 constexpr int VALUE_LDS_WORDS = VALUE_MAX * POLICY_F + VALUE_MAX;
 constexpr int FRAME_SCORES = VALUE_MAX;
+
+// Pinned words of a context that a training step writes (theta, then the
+// loss), so that reading them back needs no copy.
+struct TrainStage {
+    std::mutex mu;
+    float *words = nullptr;
+};
 
 }  // namespace cubics

@@ -29,6 +29,19 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+// Copies of the gradient kernel's sums (each POLICY_NP + 1 floats) and their
+// distance in floats.
+constexpr int GRAD_COPIES = 8, GRAD_STRIDE = 512;
+
+// Adam's state and step (theta == nullptr: gradient only).
+struct AdamArgs {
+    float *theta, *m, *v;
+    uint16_t *w1b, *w2b;
+    float *theta_host, *loss_host;  // in pinned host memory
+    float lr, beta1, beta2, eps;
+    int step;
+};
+
 // One 16-row tile.  xT: this lane's B operand of layer 1, i.e. the bf16 bits
 // of X[row = lane % 16][feature = 4 (lane / 16) + j].  Returns layer 2's
 // accumulator: lanes with lane % 16 == 0 hold y (without b2) of rows
