@@ -123,10 +123,11 @@ struct QView {
     unsigned long long word; unsigned long long _p[15];
 };
 struct QBlock {
-    QGlobal g;
     QCtl ring[MAX_RINGS];
     QView view[QVIEWS];
+    QGlobal g;  // last: read back together with the instances' counters behind it
 };
+static_assert(sizeof(QBlock) % 128 == 0, "the instances' counters behind it start a line");
 
 constexpr uint32_t SIG_IDLE_MASK = 0x00FFFFFFu;
 constexpr uint32_t SIG_DONE = 1u << 29;  // some instance's done flag is set
