@@ -42,6 +42,14 @@ struct AdamArgs {
     int step;
 };
 
+// Four weights as two words (weights start on a word and are padded to one).
+__device__ __forceinline__ bf16x4 ld_bf4(const uint16_t *p) {
+    typedef uint32_t __attribute__((may_alias)) word;
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 v = {((const word *)p)[0], ((const word *)p)[1]};
+    return __builtin_bit_cast(bf16x4, v);
+}
+
 // One 16-row tile.  xT: this lane's B operand of layer 1, i.e. the bf16 bits
 // of X[row = lane % 16][feature = 4 (lane / 16) + j].  Returns layer 2's
 // accumulator: lanes with lane % 16 == 0 hold y (without b2) of rows
@@ -56,10 +64,8 @@ __device__ __forceinline__ f32x4 mlp_tile(const PolicyDev &P, bf16x4 xT, int lan
     f32x4 acc2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll(COMPACT ? 1 : 4)
     for (int t = 0; t < 4; ++t) {
-        bf16x4 a1;
-        const uint16_t *w = P.w1 + (size_t)(16 * t + col) * MLP_FPAD + 4 * kq;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) a1[j] = (short)w[j];
+        const bf16x4 a1 = ld_bf4(P.w1 + (size_t)(16 * t + col) * MLP_FPAD + 4 * kq);
+        const bf16x4 w2 = ld_bf4(P.w2 + 16 * t + 4 * kq);
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         const f32x4 d1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, xT, zero, 0, 0, 0);
         bf16x4 a2, b2;
@@ -69,7 +75,7 @@ __device__ __forceinline__ f32x4 mlp_tile(const PolicyDev &P, bf16x4 xT, int lan
             const float p = d1[r] + P.b1[h];
             if (pre) pre[4 * t + r] = p;
             a2[r] = (short)f2bf(p > 0.f ? p : 0.f);
-            b2[r] = (short)(col == 0 ? P.w2[h] : (uint16_t)0);
+            b2[r] = col == 0 ? w2[r] : (short)0;
         }
         acc2 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a2, b2, acc2, 0, 0, 0);
     }

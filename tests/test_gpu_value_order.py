@@ -155,3 +155,41 @@ def test_trained_value_order_reaches_first_solutions_sooner(ctx, cb):
 def json_line(rep):
     import json
     return json.dumps({k: v for k, v in rep.items() if k != "theta"})
+
+
+@pytest.mark.parametrize("n,d", [(2, 64), (5, 5), (6, 33), (9, 32), (64, 6), (65, 40), (66, 33), (130, 5)])
+def test_value_features_at_edges(ctx, cb, n, d):
+    """Any number of tables at a variable (one, around four rows in flight,
+    around the 64 units loaded at once), one word and two, domains with gaps
+    and an empty one.  Tolerance: a quotient and a sum of up to 129 of them in
+    fp32, 130 x 2^-24 < 1e-5."""
+    inst = cspgen.rb(n * 100 + d, n=n, d=d, dens_pm=1000, tight_pm=400)
+    W = (d + 31) // 32
+    rng = np.random.default_rng(n + d)
+    allowed = rng.random((n, 32 * W)) < 0.6
+    allowed[:, d:] = False
+    allowed[0, :2] = True
+    if n > 2:
+        allowed[n - 1] = False
+    dom = np.packbits(allowed, axis=1, bitorder="little").view(np.uint32)
+    got = ctx.value_features(ctx.load(inst), np.ascontiguousarray(dom), depth=2, x=0)
+    fracs = []
+    for c in range(inst.m):
+        i, j = (int(v) for v in inst.scope(c))
+        if 0 not in (i, j):
+            continue
+        Wj = (int(inst.dsize[j]) + 31) // 32
+        tab = np.asarray(inst.tab(c), dtype=np.uint32).reshape(-1, Wj)
+        bits = np.unpackbits(tab.view(np.uint8), axis=1, bitorder="little")[:, :d]
+        t, bits = (j, bits) if i == 0 else (i, bits.T)
+        live = allowed[t, :d]
+        if live.any():
+            fracs.append(bits[:, live].sum(1) / live.sum())
+    size = allowed[0].sum()
+    for a in range(32 * W):
+        if not allowed[0, a]:
+            assert np.all(got[a] == 0)
+            continue
+        fr = [f[a] for f in fracs]
+        want = [a / d, np.mean(fr) if fr else 1.0, min(fr) if fr else 1.0, 2 / n, size / d]
+        assert np.allclose(got[a], want, rtol=1e-5, atol=1e-5), (a, got[a], want)
