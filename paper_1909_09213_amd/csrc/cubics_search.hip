@@ -111,9 +111,6 @@ DEV u64 wave_min64(u64 v) {
 }
 
 // -------------------------------------------------------------- atomics
-DEV uint32_t ld_acq(uint32_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-}
 DEV uint32_t ld_rlx(uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -122,9 +119,6 @@ DEV int ld_rlx_i(int32_t *p) {
 }
 DEV u64 ld_rlx_u64(u64 *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-DEV void st_rel(uint32_t *p, uint32_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 DEV void st_rel_i(int32_t *p, int v) {
     __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -142,8 +136,7 @@ DEV void st_rlx_u64(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, 
 DEV void st_rlx(uint32_t *p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// device-scope fences: acquire invalidates, release writes back this XCD's L2
-DEV void fence_acq() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
+// device-scope release: writes back this XCD's L2
 DEV void fence_rel() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent"); }
 // Queue slots move between XCDs through device-coherent (agent-scope)
 // accesses only, so handing one over needs no write-back of the producer's
@@ -159,10 +152,6 @@ DEV void slot_stores_done() {
 DEV void slot_claimed() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); }
 DEV u64 add_u64(u64 *p, u64 v) {
     return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-DEV bool cas_u32(uint32_t *p, uint32_t *expected, uint32_t desired) {
-    return __hip_atomic_compare_exchange_strong(p, expected, desired, __ATOMIC_RELAXED,
-                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // workgroup-scope words in LDS (the idle-poll token)
 DEV bool lds_take(uint32_t *p) {
@@ -2943,7 +2932,11 @@ DEV InstDev rebase(const InstDev &g, const uint32_t *tab) {
 // the global queue until no task is pending anywhere.  TL: a single-instance
 // solve whose packed tables are staged once per workgroup in LDS.
 template <int WM, bool TL, int FEAT, bool GLOB, bool SEGC, bool VAR = false>
-__global__ __launch_bounds__(512, VAR ? CUBICS_LB_WAVES_VAR : (WM > 2 ? 1 : FEAT == 0 && !GLOB && !SEGC ? CUBICS_LB_WAVES_PLAIN : CUBICS_LB_WAVES)) void search_kernel(SearchParams P) {
+__global__ __launch_bounds__(512, VAR                             ? CUBICS_LB_WAVES_VAR
+                                  : WM > 2                        ? 1
+                                  : FEAT == 0 && !GLOB && !SEGC   ? CUBICS_LB_WAVES_PLAIN
+                                                                  : CUBICS_LB_WAVES)
+void search_kernel(SearchParams P) {
     // 16-byte alignment: the words behind hold 64-bit sets that lanes update
     // with 64-bit atomics, and the tables are staged by 16-byte stores
     extern __shared__ __align__(16) uint32_t lds_raw[];
