@@ -208,6 +208,8 @@ extern "C" void cubics_cancel(cubics_ctx *c) {
 }
 
 // -------------------------------------------------------------------- load
+static_assert(TEAM_CHILDREN == CUBICS_MAX_DOMAIN, "a branching's children");
+
 namespace {
 
 struct Packer {
@@ -991,14 +993,14 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
     P.nblocks = blocks;
     P.ring_workers = (nworkers + nrings - 1) / nrings;
     // Exhaustive searches start with every worker on a share of its ring's
-    // first instances, if there are at least two workers for each and every
-    // ring has workgroups enough to give each of its instances one.  A
-    // find-first search keeps the depth-first start: its first descent alone
-    // often meets a solution.
+    // first instances, if there are at least two workers, every ring has
+    // workgroups enough to give each of its instances one, and no team is too
+    // large.  A find-first search keeps the depth-first start: its first descent
+    // alone often meets a solution.
     {
         const int per_ring = nrings > 1 ? std::min(gang, (B + nrings - 1) / nrings) : B;
         P.team = mode != CUBICS_MODE_FIRST && L0.donate && L0.split_target == 0 && feat != 2 && nworkers >= 2 &&
-                 blocks / nrings >= per_ring;
+                 blocks / nrings >= per_ring && team_allowed(team_size(blocks, wpb, nrings, B, gang));
     }
     P.donate = L0.donate ? 1 : 0;
     P.split_target = L0.split_target;

@@ -129,6 +129,27 @@ struct QBlock {
 };
 static_assert(sizeof(QBlock) % 128 == 0, "the instances' counters behind it start a line");
 
+// A team (the workers that start one instance together) of `size` members
+// divides itself over the m children of a branching (m < size): child k takes
+// members [team_first(k), team_first(k + 1)), so member `rank` takes child
+// team_child_of(rank).  The products have to stay within 32 bits: an instance
+// whose workers would make a larger team than TEAM_MAX starts from one worker
+// (at 9,000,000 members and 256 children they wrap, and 17 of the 256 values
+// have no member).
+constexpr int TEAM_MAX = 1 << 22;
+constexpr int TEAM_CHILDREN = 256;  // the widest domain (CUBICS_MAX_DOMAIN)
+static_assert((long long)TEAM_MAX * TEAM_CHILDREN + TEAM_CHILDREN < (1LL << 31), "32-bit products");
+constexpr int team_child_of(int rank, int size, int m) { return rank * m / size; }
+constexpr int team_first(int k, int size, int m) { return (k * size + m - 1) / m; }
+// The members of the largest team when `blocks` workgroups of wpb workers on
+// `rings` rings start B instances, `active` a ring (rings > 1).
+constexpr long long team_size(long long blocks, int wpb, int rings, long long B, long long active) {
+    const long long ring_blocks = (blocks + rings - 1) / rings;
+    const long long slots = rings == 1 ? B : (active < B / rings ? active : B / rings);
+    return (ring_blocks + slots - 1) / slots * wpb;
+}
+constexpr bool team_allowed(long long size) { return size <= TEAM_MAX; }
+
 constexpr uint32_t SIG_IDLE_MASK = 0x00FFFFFFu;
 constexpr uint32_t SIG_DONE = 1u << 29;  // some instance's done flag is set
 constexpr uint32_t SIG_STOP = 1u << 30;  // the whole launch stops

@@ -1712,8 +1712,8 @@ struct Team {
 // (Integer division runs on the vector unit: uni() keeps its results, and
 // all that is derived from them, in scalar registers.)
 DEV int team_child(Team &T, int m) {
-    const int k = uni(T.rank * m / T.size);
-    const int lo = uni((k * T.size + m - 1) / m), hi = uni(((k + 1) * T.size + m - 1) / m);
+    const int k = uni(team_child_of(T.rank, T.size, m));
+    const int lo = uni(team_first(k, T.size, m)), hi = uni(team_first(k + 1, T.size, m));
     T.rank -= lo;
     T.size = hi - lo;
     return k;
