@@ -249,7 +249,8 @@ int cubics_root(cubics_prob *prob, int32_t layout, uint32_t *out_bits, int32_t *
    which changes the order of the search but never its result.
    Hitting max_nodes / max_solutions / time_ms is a verdict (LIMIT), not an
    error.  Workers check them periodically: max_nodes every 128 nodes of a
-   worker, so a search may run up to 128 nodes per worker past it; a stop
+   worker and before it takes up a task, so a search may run up to 128 nodes per
+   worker past it (and is complete if its tree ends there unchecked); a stop
    (time_ms, cancel, another worker's find-first solution) is seen about
    every 100 us of a worker's own time, at its next node (the register layout:
    within 16 nodes), the clock and the cancel flag about every millisecond.

@@ -995,12 +995,14 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
     // Exhaustive searches start with every worker on a share of its ring's
     // first instances, if there are at least two workers, every ring has
     // workgroups enough to give each of its instances one, and no team is too
-    // large.  A find-first search keeps the depth-first start: its first descent
+    // large (also for its instance's node budget).  A find-first search keeps the depth-first start: its first descent
     // alone often meets a solution.
     {
         const int per_ring = nrings > 1 ? std::min(gang, (B + nrings - 1) / nrings) : B;
         P.team = mode != CUBICS_MODE_FIRST && L0.donate && L0.split_target == 0 && feat != 2 && nworkers >= 2 &&
-                 blocks / nrings >= per_ring && team_allowed(team_size(blocks, wpb, nrings, B, gang));
+                 blocks / nrings >= per_ring;
+        for (int b = 0; b < B && P.team; ++b)
+            P.team = team_allowed(team_size(blocks, wpb, nrings, B, gang), inst[b].max_nodes);
     }
     P.donate = L0.donate ? 1 : 0;
     P.split_target = L0.split_target;

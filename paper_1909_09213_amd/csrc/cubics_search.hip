@@ -1567,12 +1567,13 @@ constexpr uint32_t VIEW_TICKS = 2000;  // 20 us of the 100 MHz wall clock
 // The register layout, where a node takes one or two microseconds, looks at
 // the clock every VAR_CHECK nodes; the LDS layouts at every node.
 constexpr int VAR_CHECK = 16;
-// Under a node budget, nodes are counted against it every ACCT_NODES nodes,
-// and in the LDS layouts also every ACCT_CLK (about 50 us) after at least
-// ACCT_MIN nodes: a node of an instance of a hundred variables takes up to a
-// hundred microseconds, and an instance shared by dozens of workers would run
-// thousands of nodes past its budget.
-constexpr int ACCT_NODES = 128;
+// Under a node budget, a worker adds its nodes to the instance's count before
+// they are more than ACCT_NODES and at the end of every task, and in the LDS
+// layouts also every ACCT_CLK (about 50 us) after at least ACCT_MIN nodes: a node
+// of an instance of a hundred variables takes up to a hundred microseconds, and
+// an instance shared by dozens of workers would run thousands of nodes past its
+// budget.  The count is compared with the budget where it is added to within a
+// task and before a task begins, so that many short tasks stay within it too.
 constexpr int ACCT_MIN = 8;
 constexpr uint32_t ACCT_CLK = 120000;
 // A frame is donated only if this many levels were seen below it in the
@@ -1581,6 +1582,23 @@ constexpr uint32_t ACCT_CLK = 120000;
 constexpr int DONATE_LEVELS = 2;
 // Longest back-off of an idle wave between two polls of its queue cell.
 constexpr int BACKOFF_MAX = 16;
+
+// The instance's nodes have reached its budget (lane 0 only).
+DEV void node_limit(const SearchParams &P, InstCtl *ctl) {
+    ctl->reason = 2;
+    st_rel_i(&ctl->done, 1);
+    signal_rings(P, SIG_DONE);
+}
+// Counts the worker's nodes against the instance's budget; true once it is used up.
+DEV bool budget_spent(const SearchParams &P, const InstDev &I, InstCtl *ctl, Counters &C, int lane) {
+    u64 tot = 0;
+    if (lane == 0) tot = add_u64(&ctl->nodes, C.nodes) + C.nodes;
+    tot = uni64(tot);
+    C.nodes = 0;
+    if (tot < I.max_nodes) return false;
+    if (lane == 0) node_limit(P, ctl);
+    return true;
+}
 
 DEV uint32_t clk() { return (uint32_t)clock64(); }
 // Have `span` clocks passed between `then` and `now`?  32-bit clocks wrap
@@ -2281,6 +2299,7 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
             }
         }
         if (at_node) {
+            ++since_acct;
             if (T.size <= 1) {
                 at_node = false;
                 continue;
@@ -2326,14 +2345,7 @@ DEV void run_task(const SearchParams &P, const InstDev &I, InstCtl *ctl, int b, 
         if (I.max_nodes && (since_acct >= ACCT_NODES - CLOSE_BUDGET || (since_acct >= ACCT_MIN && now - last_acct >= ACCT_CLK))) {
             since_acct = 0;
             last_acct = now;
-            u64 tot = 0;
-            if (lane == 0) tot = add_u64(&ctl->nodes, C.nodes) + C.nodes;
-            tot = uni64(tot);
-            C.nodes = 0;
-            if (tot >= I.max_nodes) {
-                if (lane == 0) { ctl->reason = 2; st_rel_i(&ctl->done, 1); signal_rings(P, SIG_DONE); }
-                return;
-            }
+            if (budget_spent(P, I, ctl, C, lane)) return;
         }
         if (now - last_poll >= POLL_CLK) {
             // nodes so long that hardly one fits between two polls are worth
@@ -2655,6 +2667,7 @@ DEV void run_task_var(const SearchParams &P, const InstDev &I, InstCtl *ctl, int
         }
         have_open = true;
         open_x = bx;
+        if (I.max_nodes) since_acct = (int)C.nodes;
     } else {
         F = F0;
         if (lane < n) trail[FRAME_HDR + lane] = d;
@@ -2823,18 +2836,11 @@ DEV void run_task_var(const SearchParams &P, const InstDev &I, InstCtl *ctl, int
         if (--until_check == 0) {
             until_check = VAR_CHECK;
             since_acct += VAR_CHECK;
-            if (since_acct >= ACCT_NODES) fold_var(C);
-            if (I.max_nodes && since_acct >= ACCT_NODES) {
-                u64 tot = 0;
-                if (lane == 0) tot = add_u64(&ctl->nodes, C.nodes) + C.nodes;
-                tot = uni64(tot);
-                C.nodes = 0;
-                if (tot >= I.max_nodes) {
-                    if (lane == 0) { ctl->reason = 2; st_rel_i(&ctl->done, 1); signal_rings(P, SIG_DONE); }
-                    return;
-                }
+            if (since_acct >= ACCT_NODES - VAR_CHECK) {
+                since_acct = 0;
+                fold_var(C);
+                if (I.max_nodes && budget_spent(P, I, ctl, C, lane)) return;
             }
-            if (since_acct >= ACCT_NODES) since_acct = 0;
             const uint32_t now = clk();
             if (now - last_poll >= POLL_CLK) {
                 last_poll = now;
@@ -3236,6 +3242,15 @@ void search_kernel(SearchParams P) {
             if (lane == 0) skip = ld_rlx_i(&ctl->done);
             skip = uni(skip);
         }
+        // (the count read ahead of the snapshot's loads cost the LDS layouts 4%
+        // of a node in registers; the wait here does not show)
+        if (!skip && I.max_nodes) {
+            if (lane == 0 && ld_rlx_u64(&ctl->nodes) >= I.max_nodes) {
+                node_limit(P, ctl);
+                skip = 1;
+            }
+            skip = uni(skip);
+        }
         if (!skip) {
             if (VAR)
                 run_task_var<WM>(P, I, ctl, b, kind, F0, T, L, trail, C, lane, t_start, &wgp);
@@ -3244,7 +3259,7 @@ void search_kernel(SearchParams P) {
         }
         C.tasks += 1;
         fold_var(C);
-        if (I.max_nodes) {  // the budget counts every node at the task's end
+        if (I.max_nodes) {  // no node is left uncounted at a task's end
             flush(ctl, nullptr, C, lane);
             held = -1;
         }
