@@ -32,6 +32,26 @@ def _free(sizes):
                            tabs=np.zeros(0, np.uint32), name="free")
 
 
+@pytest.mark.parametrize("two_way", [False, True])
+@pytest.mark.parametrize("sizes", [(2, 3, 5, 7, 30), (2, 9, 31), (3, 4, 31, 31), (2, 30, 200)])
+@pytest.mark.parametrize("layout", [1, 2, 3])
+def test_one_worker_stops_within_128_nodes(ctx, cb, layout, sizes, two_way):
+    """Also where the last open variable has more values than a node under a
+    budget may close."""
+    inst = _free(sizes)
+    ref = oracle.solve(inst, oracle.MODE_COUNT, two_way=two_way)
+    p = ctx.load(inst)
+    for budget in (1, 31, 96, 127, 128, 129, 300, 500, ref.nodes - 129):
+        if budget + 128 >= ref.nodes:
+            continue
+        r = ctx.solve(p, cb.MODE_COUNT, layout=layout, workers=1, max_nodes=budget, two_way=two_way)
+        assert r.verdict == "LIMIT" and budget <= r.nodes < budget + 128, budget
+        assert r.count < ref.count
+    for budget in (ref.nodes + 1, 10 * ref.nodes):
+        r = ctx.solve(p, cb.MODE_COUNT, layout=layout, workers=1, max_nodes=budget, two_way=two_way)
+        assert (r.verdict, r.count, r.nodes, r.fails) == ("SAT", ref.count, ref.nodes, 0)
+
+
 @pytest.fixture(scope="module")
 def large():
     """A tree of 1.1e6 nodes."""
