@@ -1001,8 +1001,10 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
         const int per_ring = nrings > 1 ? std::min(gang, (B + nrings - 1) / nrings) : B;
         P.team = mode != CUBICS_MODE_FIRST && L0.donate && L0.split_target == 0 && feat != 2 && nworkers >= 2 &&
                  blocks / nrings >= per_ring;
+        const long long size = team_size(blocks, wpb, nrings, B, gang);
+        if (!team_allowed(size)) P.team = 0;
         for (int b = 0; b < B && P.team; ++b)
-            P.team = team_allowed(team_size(blocks, wpb, nrings, B, gang), inst[b].max_nodes);
+            if (!team_in_budget(size, inst[b].max_nodes)) P.team = 0;
     }
     P.donate = L0.donate ? 1 : 0;
     P.split_target = L0.split_target;

@@ -148,6 +148,7 @@ constexpr long long team_size(long long blocks, int wpb, int rings, long long B,
     const long long slots = rings == 1 ? B : (active < B / rings ? active : B / rings);
     return (ring_blocks + slots - 1) / slots * wpb;
 }
+constexpr bool team_allowed(long long size) { return size <= TEAM_MAX; }
 // Nodes a worker may search before it counts them against a node budget.
 constexpr int ACCT_NODES = 128;
 // May a team of this size start an instance under a node budget (0 = none)?  All
@@ -156,8 +157,8 @@ constexpr int ACCT_NODES = 128;
 // tree has counted most of what it gives away.  A budget of 1,000 nodes on a tree
 // of 1.1e6, every worker of the device: 1,560 to 2,110 nodes from one worker,
 // 12,700 to 102,000 from a team; a tree of 2^18 nodes was searched whole.)
-constexpr bool team_allowed(long long size, unsigned long long max_nodes) {
-    return size <= TEAM_MAX && (max_nodes == 0 || max_nodes / (8 * ACCT_NODES) >= (unsigned long long)size);
+constexpr bool team_in_budget(long long size, unsigned long long max_nodes) {
+    return max_nodes == 0 || max_nodes / (8 * ACCT_NODES) >= (unsigned long long)size;
 }
 
 constexpr uint32_t SIG_IDLE_MASK = 0x00FFFFFFu;
