@@ -955,8 +955,13 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
     d_ctl = (char *)d_q + ctl_off;
 
     const size_t back = ctl_off + sizeof(InstCtl) * (size_t)B - g_off;
-    if ((rc = ctx->up.ensure(sizeof(InstDev) * (size_t)B)) || (rc = ctx->down.ensure(back + 8))) return rc;
-    InstDev *inst = (InstDev *)ctx->up.p;
+    // (the allocation-free call asks the runtime for nothing, pinned memory
+    // neither: its copies go through pageable memory)
+    std::vector<InstDev> pageable_up(static_scratch ? (size_t)B : 0);
+    std::vector<unsigned long long> pageable_down(static_scratch ? (back + 15) / 8 : 0);
+    if (!static_scratch)
+        if ((rc = ctx->up.ensure(sizeof(InstDev) * (size_t)B)) || (rc = ctx->down.ensure(back + 8))) return rc;
+    InstDev *inst = static_scratch ? pageable_up.data() : (InstDev *)ctx->up.p;
     for (int b = 0; b < B; ++b) {
         const cubics_limits &Lb = lims ? lims[b] : dflt;
         inst[b] = probs[b]->dev;
@@ -1062,7 +1067,7 @@ static int solve_impl(cubics_prob *const *probs, int B, int mode, const cubics_l
         HIPCHK(launch_search(G.wmax, P, blocks, wpb, lds, tl, variant, st));
         HIPCHK(hipEventRecord(ctx->ev1, st));
     }
-    char *down = (char *)ctx->down.p;
+    char *down = static_scratch ? (char *)pageable_down.data() : (char *)ctx->down.p;
     unsigned long long *traces = (unsigned long long *)(down + back);
     *traces = 0;
     if (P.trace_out) HIPCHK(hipMemcpyAsync(traces, ctx->tracecnt.p, 8, hipMemcpyDeviceToHost, st));
