@@ -198,9 +198,6 @@ def test_features_match_their_definition(ctx, cb):
     assert np.all(got0[:, 3] == 0)
 
 
-@pytest.mark.skip(reason="hung the device twice while a team's share could wait for a workgroup that was not "
-                         "resident; the shares are claimed now, and this case stays off the device until that "
-                         "mend has been reviewed")
 def test_trained_policy_gains_over_first_fail(ctx, cb):
     """Train on sibling subtree sizes at nodes of 600 seeded instances, then
     count 256 held-out instances under first-fail and under the policy (same

@@ -69,4 +69,25 @@ def test_more_workers_than_a_team_holds():
     print("nine million workers", flush=True)
     r = ctx.solve(ctx.load(inst), cb.MODE_COUNT, layout=cb.LAYOUT_LANE, workers=9_000_000)
     assert (r.verdict, r.count, r.nodes, r.fails) == ("SAT", 1536, 1 + 2 + 6 + 1536, 0)
-    ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch", [1, 4])
+def test_learned_branching_with_more_workers_than_fit(batch):
+    """The learned kernel, whose workgroups hold the networks in LDS and of which
+    the fewest fit at once: late workgroups must not be waited for, and each
+    team's members choose the same variable at the same node."""
+    import oracle
+    from paper_1909_09213_amd import cubics as cb, learn
+    insts = learn.instances(cspgen.SEED_EVAL, 12)
+    refs = [oracle.solve(x, oracle.MODE_COUNT, max_nodes=300000) for x in insts]
+    insts, refs = zip(*[(x, r) for x, r in zip(insts, refs) if r.verdict != "LIMIT"][:batch])
+    assert len(insts) == batch
+    ctx = cb.Context(0)
+    probs, pol = [ctx.load(x) for x in insts], cb.Policy(ctx, learn.init_theta(1))
+    for workers in (1, 30001, 0):
+        print("learned, late", batch, workers, flush=True)
+        res = ctx.solve_batch(probs, cb.MODE_COUNT, branching=cb.BRANCH_LEARNED, policy=pol, workers=workers,
+                              layout=cb.LAYOUT_LANE)
+        for r, ref in zip(res, refs):
+            assert (r.verdict, r.count) == (ref.verdict, ref.count)
