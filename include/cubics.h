@@ -98,7 +98,8 @@ enum { CUBICS_BRANCH_FIRST_FAIL = 0, CUBICS_BRANCH_LEARNED = 1 };
          1 + sum_i (d_i - 1) <= 64; other cases fall back to LANE);
    AUTO  the autotuned choice (layout and worker count) for the instance's
          shape, else VAR for a single instance whose tables fit in LDS, else
-         SEG for domains wider than 24 values, else LANE. */
+         SEG for domains wider than 24 values, else LANE (cubics_root: always
+         LANE). */
 enum { CUBICS_LAYOUT_AUTO = 0, CUBICS_LAYOUT_LANE = 1, CUBICS_LAYOUT_SEG = 2, CUBICS_LAYOUT_VAR = 3 };
 
 /* Supported range: 1 <= d_i <= 256 values per variable (at most 8 32-bit
@@ -194,7 +195,8 @@ const char *cubics_last_error(void);
 
 /* Create a context on HIP device `device`, issuing work on `hip_stream`
    (a hipStream_t; NULL = the null stream).  The context owns scratch device
-   memory (work queue, trail stacks) that grows on demand. */
+   memory (work queue, trail stacks) and pinned host memory (descriptors,
+   counters) that grow on demand. */
 int cubics_create(int32_t device, void *hip_stream, cubics_ctx **out);
 void cubics_destroy(cubics_ctx *ctx);
 int cubics_set_stream(cubics_ctx *ctx, void *hip_stream);

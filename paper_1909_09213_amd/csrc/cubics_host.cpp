@@ -734,7 +734,12 @@ int choose_layout(cubics_prob *const *probs, int B, int requested) {
         return requested;
     // AUTO: the autotuned choice of the first instance's shape bucket, else a
     // rule: registers when the instance is small enough, lane-per-value
-    // segments once domains are wide
+    // segments once domains are wide.  The second line dates from LANE
+    // revisions that walked the whole union of the source's rows; against the
+    // present ones it costs, and autotuning or asking for LANE avoids it (counts
+    // of n=40 density 0.2 tightness 0.35 under a budget, LANE against SEG: 64
+    // instances 212 and 124 nodes/us at d=26, 164 and 73 at d=64; one instance
+    // 380 and 258, 235 and 164)
     cubics_ctx *ctx = probs[0]->ctx;
     auto it = ctx->tuned.find(probs[0]->bucket);
     if (it != ctx->tuned.end()) return it->second.layout;
@@ -1301,8 +1306,10 @@ extern "C" int cubics_root(cubics_prob *p, int32_t layout, uint32_t *out_bits, i
     SearchParams P;
     memset(&P, 0, sizeof P);
     P.inst = (const InstDev *)ctx->inst.p;
-    // (one lane per unit unless the caller asks otherwise: every variable is
-    // dirty at a root, and most units are looked at without reading a row)
+    // (one lane per unit unless the caller asks otherwise, whatever is tuned for
+    // searches: every variable is dirty at a root, and most units are looked at
+    // without reading a row; n=120 d=64: 0.17 ms,
+    // SEG 3.7)
     P.layout = layout == CUBICS_LAYOUT_AUTO ? CUBICS_LAYOUT_LANE : choose_layout(arr, 1, layout);
     P.lds_words = G.lds_words;
     P.nmax = G.nmax;

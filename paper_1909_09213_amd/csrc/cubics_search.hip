@@ -516,7 +516,7 @@ DEV int unit_limit(const Unit &u) { return (int)((uint32_t)u.src >> 16); }
 // The lanes left out load no rows: scattered row loads, one cache access a
 // lane and row, bound the search of instances whose tables lie in memory.
 // 1,024 sweep instances 320 -> 290 ms, a root of 120 variables with 64 values
-// 6.6 -> 0.22 ms.  (Rows in LDS are cheaper than the test: not used there.)
+// 0.27 -> 0.17 ms (SEG: 6.3 -> 3.7).  (Rows in LDS are cheaper than the test: not used there.)
 DEV bool may_remove(const Unit &u, int ps, int pt) { return ps <= unit_limit(u) && (pt >= 2 || ps == 1); }
 
 // Process one chunk of binary units in LANE layout.  Returns wave-uniform fail.
@@ -1294,9 +1294,10 @@ DEV int node_test(const InstDev &I, const Lds &L, int lane, int *bx, bool *one) 
 // propagator is exact with one open variable), and the constraints without x
 // hold.  None of the nodes below fails, propagating them would change nothing,
 // and there are k: d-way the k children, all solutions; 2-way 2 (k - 1) nodes
-// with k solutions (x = a, then x != a, down to the last value).  Only where solutions are counted and not stored
-// or capped, and not while subtree sizes are recorded; under a node budget
-// (checked every ACCT_NODES nodes) for at most CLOSE_BUDGET nodes.
+// with k solutions (x = a, then x != a, down to the last value).  Only where
+// solutions are counted and not stored or capped, and not while subtree sizes
+// are recorded; under a node budget (checked every ACCT_NODES nodes) for at most
+// CLOSE_BUDGET nodes.
 // RB n=40 d=16 slice of 1.34e10 nodes, 9.75e9 of them solutions: 3.2 -> 1.0 s;
 // a slice of the n=200 d=256 family (2.2e5 solutions) 31.7 -> 1.1 ms.
 DEV bool counts_only(const SearchParams &P, const InstDev &I) {
@@ -1308,9 +1309,11 @@ constexpr int CLOSE_BUDGET = 32;
 // ------------------------------------------------------------- queue
 
 // Bounded MPMC ring (per-cell sequence numbers; Vyukov's bounded queue).
-// Called by lane 0 only.  Every poll uses relaxed loads, so idle workers never
-// invalidate caches; a successful pop or reserve is followed by one acquire
-// fence, and publishing is preceded by one release fence.
+// Called by lane 0 only.  Sequence words and slots are accessed device-coherently
+// (agent scope, relaxed), so neither a poll nor a hand-over touches a cache as a
+// whole: a producer waits for the acknowledgement of its slot stores before it
+// publishes the sequence word (slot_stores_done), and what follows a claimed or
+// reserved cell is only kept behind it in program order (slot_claimed).
 // Consumers take tickets: an idle wave claims the next position with one
 // fetch-add on the head and waits on that position's own sequence word until
 // a producer publishes it.  Compare-and-swap pops made every polling wave
@@ -1554,8 +1557,10 @@ DEV void flush(InstCtl *ctl, WgSum *sum, Counters &C, int lane) {
 // workgroups that share one of QVIEWS copies in memory only the one that finds
 // the copy VIEW_TICKS old reads the word itself: one address answers some
 // 10^8 loads a second, and 1,280 workgroups that read it every 20 us held up
-// every hand-over.  (768 labels on 5,120 workers: 17.7 ms without the copies,
-// 8.9 with them; with polls every 40 and 80 us 7.7 and 6.3 ms.)  The view holds the stop
+// every hand-over.  (768 labels on 5,120 workers: 17.7 ms without the copies, 8.9
+// with them at the time; now 8.5 ms with polls every 20 us, 7.5 at 40, 6.5 at 80
+// and 6.4 at 160, where the count of 13-queens takes 0.81 ms instead of 0.69.)
+// The view holds the stop
 // flags and the odds (of 65536) with which a busy wave should donate: the idle
 // waves over the busy ones, so that a few idle waves do not make every busy
 // one give work away.
@@ -1720,7 +1725,7 @@ DEV void nth_value(const uint32_t (&v)[WM], int k, uint32_t (&one)[WM]) {
 // Before, one worker opened the tree and gave a frame away every 128 nodes
 // (2048 in the register layout), and a frame went as a whole: with the polls
 // below and half-frame donations, 13-queens with 8 blocked squares (3.4e5
-// nodes) went from 89 to 1.4 ms, RB n=40 d=16 tightness 0.40 (1e5..1e6 nodes)
+// nodes) went from 93 to 1.4 ms, RB n=40 d=16 tightness 0.40 (1e5..1e6 nodes)
 // from 379 to 9 ms, a batch of 768 labels from 78 to 16 ms, 48 global twins
 // from 177 to 22 ms; the RB slice of 1.34e10 nodes from 3.5 to 3.2 s.
 struct Team {

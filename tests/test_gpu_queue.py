@@ -66,8 +66,9 @@ def test_time_limit_stops_and_drains(ctx, cb, layout):
     r = ctx.solve(p, cb.MODE_COUNT, layout=layout, time_ms=200)
     assert r.verdict == "LIMIT"
     assert 0 < r.nodes < 13383873410
-    # the stop is seen within 2048 nodes of every worker; the queued tasks
-    # are then claimed and skipped
+    # the stop is seen within about 100 us of every worker's own time, the clock
+    # that causes it within a millisecond; the queued tasks are then claimed
+    # and skipped
     assert r.kernel_ms < 1200, r.kernel_ms
     # the context stays usable: a complete small search right after
     q = ctx.load(cspgen.queens(8))
