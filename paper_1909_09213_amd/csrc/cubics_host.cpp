@@ -1308,8 +1308,7 @@ extern "C" int cubics_root(cubics_prob *p, int32_t layout, uint32_t *out_bits, i
     P.inst = (const InstDev *)ctx->inst.p;
     // (one lane per unit unless the caller asks otherwise, whatever is tuned for
     // searches: every variable is dirty at a root, and most units are looked at
-    // without reading a row; n=120 d=64: 0.17 ms,
-    // SEG 3.7)
+    // without reading a row; n=120 d=64: 0.17 ms, SEG 3.7)
     P.layout = layout == CUBICS_LAYOUT_AUTO ? CUBICS_LAYOUT_LANE : choose_layout(arr, 1, layout);
     P.lds_words = G.lds_words;
     P.nmax = G.nmax;
