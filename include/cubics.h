@@ -277,8 +277,8 @@ int cubics_solve_batch(cubics_prob *const *probs, int32_t B, int32_t mode,
    launch (instance descriptors, per-instance counters, the work queue, the
    workers' trail stacks) comes from a static device array of
    CUBICS_STATIC_SCRATCH_MIB MiB that each GPU holds from its first use until
-   the process ends; the call allocates no device memory itself (the
-   problems, the context and the caller's solution buffers exist already).
+   the process ends; the call allocates no device memory itself, and no
+   pinned host memory (the problems, the context and the caller's solution buffers exist already).
    The worker count shrinks until the trails fit the array, so a launch may
    run on fewer workers than cubics_solve_batch would use.  Errors: as
    cubics_solve_batch, plus EUNSUPPORTED when even one worker does not fit
